@@ -532,13 +532,22 @@ void build_chunks(Phase& ph, int chunk_rows, const std::vector<int>& pt_off, int
     }
 }
 
+// float32 problems on the matrix cores, everything else (and simple_only) on the plain kernel
+void launch_gemm_other(cf_ctx* c, const void* A, const void* W, const void* W2, float* Cf, void* Dt, int M, int N,
+                       int K, int epi) {
+    if (!c->simple_only && c->m.dtype == CF_F32 && gemm_f32_supported(A, W, W2, K))
+        launch_gemm_f32(c->cs, A, W, W2, epi == EPI_STORE_F32 || epi == EPI_ADD_F32 ? Cf : (float*)Dt, M, N, K, epi);
+    else
+        launch_gemm_simple(c->cs, c->m.dtype, A, W, W2, Cf, Dt, M, N, K, epi);
+}
+
 void gemm(cf_ctx* c, int cls, const void* A, const void* W, const void* W2, float* Cf, void* Dt,
           int M, int N, int K, int epi) {
     c->prof_begin(cls, 2.0 * M * (double)N * K * (epi == EPI_SILU_MUL ? 2 : 1), c->cs);
     if (!c->simple_only && gemm_mfma_supported(c->m.dtype, M, N, K, epi))
         launch_gemm_mfma(c->cs, A, W, W2, Cf, Dt, M, N, K, epi);
     else
-        launch_gemm_simple(c->cs, c->m.dtype, A, W, W2, Cf, Dt, M, N, K, epi);
+        launch_gemm_other(c, A, W, W2, Cf, Dt, M, N, K, epi);
     c->prof_end(cls, c->cs);
 }
 
@@ -720,6 +729,9 @@ int run_phase(cf_ctx* c, cf_cache* cache, const Phase& ph, int n_layers_max,
                         launch_attention_mfma(c->cs, c->q(), c->o(), c->attn_part(), pool_layer,
                                               d_work + ci.work_off + w0, w1 - w0, d_grp + ci.grp_off + g0,
                                               g1 - g0, d_pt, m.n_q_heads, g);
+                    else if (!c->simple_only && m.dtype == CF_F32)
+                        launch_attention_f32(c->cs, c->q(), c->o(), pool_layer, d_work + ci.work_off + w0, w1 - w0,
+                                             d_pt, m.n_q_heads, g);
                     else
                         launch_attention_simple(c->cs, m.dtype, c->q(), c->o(), pool_layer,
                                                 d_work + ci.work_off + w0, w1 - w0, d_pt, m.n_q_heads, g);
@@ -2567,6 +2579,7 @@ extern "C" int cf_op_gemm(cf_ctx* c, const void* A, const void* W, const void* W
     CF_HIP(hipEventRecord(c->ev_t0, c->cs));
     for (int i = 0; i < reps; ++i) {
         if (use_mfma) launch_gemm_mfma(c->cs, A, W, W2, Cf, Dt, M, N, K, epi);
+        else if (impl == 0) launch_gemm_other(c, A, W, W2, Cf, Dt, M, N, K, epi);
         else launch_gemm_simple(c->cs, c->m.dtype, A, W, W2, Cf, Dt, M, N, K, epi);
     }
     CF_HIP(hipEventRecord(c->ev_t1, c->cs));

@@ -71,6 +71,11 @@ void launch_rmsnorm(hipStream_t s, int dtype, float* h, const float* delta, cons
 // A[M,K], W[N,K] (and W2) in the model dtype; Cf float [M,N] or Dt model dtype [M,N].
 void launch_gemm_simple(hipStream_t s, int dtype, const void* A, const void* W, const void* W2,
                         float* Cf, void* Dt, int M, int N, int K, int epi);
+// float32 on the matrix cores (f32_mfma.hip): rows of whole 16-byte vectors, 16-byte aligned operands.
+// C is float [M,N] for every epilogue.
+bool gemm_f32_supported(const void* A, const void* W, const void* W2, int K);
+void launch_gemm_f32(hipStream_t s, const void* A, const void* W, const void* W2, float* C, int M, int N, int K,
+                     int epi);
 // true if the MFMA kernel supports this problem (bf16, aligned K)
 bool gemm_mfma_supported(int dtype, int M, int N, int K, int epi);
 void gemm_mfma_force_tile(int tile);   // 0 = heuristic, 256 or 128 = forced (tuning)
@@ -100,6 +105,9 @@ void launch_rope_write(hipStream_t s, int dtype, const float* qkv, const int32_t
 void launch_attention_simple(hipStream_t s, int dtype, const void* q, void* out,
                              const void* pool_layer, const AttnWork* work, int n_work,
                              const int32_t* page_tables, int n_q_heads, KvGeom g);
+// float32 pages on the matrix cores, head_dim 64 or 128; items cover their whole key range (no parts)
+void launch_attention_f32(hipStream_t s, const void* q, void* out, const void* pool_layer, const AttnWork* work,
+                          int n_work, const int32_t* page_tables, int n_q_heads, KvGeom g);
 bool attention_mfma_supported(int dtype, int head_dim, int n_q_heads, int n_kv_heads);
 // query heads one workgroup of the MFMA attention kernel works on (they share the K/V tiles)
 int attention_mfma_heads_per_block(int n_q_heads, int n_kv_heads);
