@@ -114,6 +114,19 @@ def test_gemm_bits_do_not_depend_on_the_tile_shape(sess, mnk):
     assert torch.equal(outs[0][lo:], Cs)
 
 
+@pytest.mark.parametrize("at_a, at_w", [(2, 0), (0, 6), (1, 0), (0, 3)])
+def test_gemm_operands_that_start_inside_a_larger_buffer(sess, at_a, at_w):
+    """Whole-dword starts take the matrix-core kernel, odd elements the plain one; 2^-24 per term."""
+    import paper_2604_25080_amd as cf
+    M, N, K = 130, 200, 192
+    g = torch.Generator().manual_seed(at_a + 10 * at_w)
+    a, w = (torch.randn(r * K + 8, generator=g).bfloat16() for r in (M, N))
+    A, W, Cf = a.cuda(), w.cuda(), torch.zeros(M, N, device="cuda")
+    sess.ctx.op_gemm(A.data_ptr() + 2 * at_a, W.data_ptr() + 2 * at_w, 0, Cf.data_ptr(), 0, M, N, K, cf.EPI_STORE_F32, 0)
+    x, y = a[at_a:at_a + M * K].view(M, K).double(), w[at_w:at_w + N * K].view(N, K).double()
+    assert bool(((Cf.cpu().double() - x @ y.t()).abs() <= K * 2.0 ** -24 * (x.abs() @ y.abs().t())).all())
+
+
 def test_gemm_mfma_refuses_what_it_cannot_tile(sess):
     import paper_2604_25080_amd as cf
     A = torch.zeros(64, 40, dtype=torch.bfloat16, device="cuda")
