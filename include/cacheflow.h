@@ -770,8 +770,8 @@ int cf_debug_force_gemm_tile(int32_t tile);
  * (the QKV / O-proj and down-proj / - / gate-up steps of a layer).
  * impl 0 = what cf_restore_batch would pick, 1 = plain FMA kernel, 2 = MFMA
  * kernel with its own tile choice, 3 / 4 / 5 = MFMA kernel forced to 256x256 /
- * 128x128 / 64x64 block tiles (epi 3 has no 64x64 tile and takes 128x128;
- * CF_ERR_UNSUPPORTED if MFMA does not take the shape), 6 = 256x256 tiles
+ * 128x128 / 64x64 block tiles (CF_ERR_UNSUPPORTED if
+ * MFMA does not take the shape), 6 = 256x256 tiles
  * whose last partial round of tiles is covered by 128x128 tiles in the same
  * launch wherever the tile count allows it (what impl 0 picks for large
  * problems; the plain 256x256 launch otherwise).  Runs `reps`

@@ -544,7 +544,7 @@ void launch_gemm_other(cf_ctx* c, const void* A, const void* W, const void* W2, 
 void gemm(cf_ctx* c, int cls, const void* A, const void* W, const void* W2, float* Cf, void* Dt,
           int M, int N, int K, int epi) {
     c->prof_begin(cls, 2.0 * M * (double)N * K * (epi == EPI_SILU_MUL ? 2 : 1), c->cs);
-    if (!c->simple_only && gemm_mfma_supported(c->m.dtype, M, N, K, epi))
+    if (!c->simple_only && gemm_mfma_takes(c->m.dtype, M, N, K))
         launch_gemm_mfma(c->cs, A, W, W2, Cf, Dt, M, N, K, epi);
     else
         launch_gemm_other(c, A, W, W2, Cf, Dt, M, N, K, epi);
@@ -2574,7 +2574,7 @@ extern "C" int cf_op_gemm(cf_ctx* c, const void* A, const void* W, const void* W
     if (impl < 0 || impl > 6) return fail(CF_ERR_INVALID_ARG, "cf_op_gemm: impl must be 0..6");
     bool mfma_ok = gemm_mfma_supported(c->m.dtype, M, N, K, epi);
     if (impl >= 2 && !mfma_ok) return fail(CF_ERR_UNSUPPORTED, "cf_op_gemm: MFMA kernel does not take this problem");
-    bool use_mfma = impl >= 2 || (impl == 0 && mfma_ok && !c->simple_only);
+    bool use_mfma = impl >= 2 || (impl == 0 && gemm_mfma_takes(c->m.dtype, M, N, K) && !c->simple_only);
     gemm_mfma_force_tile(impl == 3 ? 256 : impl == 4 ? 128 : impl == 5 ? 64 : impl == 6 ? 257 : 0);
     struct Reset { ~Reset() { gemm_mfma_force_tile(0); } } reset_on_exit;
     CF_HIP(hipEventRecord(c->ev_t0, c->cs));

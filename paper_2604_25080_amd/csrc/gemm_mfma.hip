@@ -65,6 +65,7 @@ __device__ __forceinline__ u32x4_t buffer_rsrc(const void* base, unsigned bytes)
     r.w = 0x00020000u;
     return r;
 }
+constexpr unsigned PAST_THE_END = 0x80000000u;    // no operand tile is that long: such an offset reads zero
 // 16 bytes per lane from the buffer straight to LDS: lane i lands at lds + 16 i.  No register is
 // written; whoever reads the LDS bytes waits for vmcnt first (wait_barrier below).
 __device__ __forceinline__ void load_to_lds(u32x4_t rsrc, unsigned voff, unsigned soff, unsigned lds) {
@@ -77,6 +78,61 @@ __device__ __forceinline__ void wait_barrier() {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(LEFT) : "memory");
     __builtin_amdgcn_sched_barrier(0);
+}
+
+// Stores a wave tile: fragment (i, j) of a lane is output row row0 + 16 i, columns col0 + 16 j + r; gate/up
+// pair: the first FN/2 fragments are gate, the rest up.  INSIDE: the tile lies wholly in the matrix.
+template <int EPI, int FM, int FN, bool INSIDE>
+__device__ __forceinline__ void store_tile(const f32x4_t (&acc)[FM][FN], float* __restrict__ Cf, bf16* __restrict__ Dt,
+                                           int M, int N, int row0, int col0) {
+    constexpr bool SILU = (EPI == EPI_SILU_MUL);
+    constexpr bool TO_F32 = (EPI == EPI_STORE_F32 || EPI == EPI_ADD_F32);
+    constexpr int FN_OUT = SILU ? FN / 2 : FN;
+    const bool vec_ok = (N & 3) == 0;             // row starts stay vector-aligned
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        const int gm = row0 + i * 16;
+        if (!INSIDE && gm >= M) continue;
+#pragma unroll
+        for (int j = 0; j < FN_OUT; ++j) {
+            const int gn = col0 + j * 16;
+            const int64_t o = (int64_t)gm * N + gn;
+            f32x4_t v = acc[i][j];
+            if constexpr (SILU) {
+                // silu(g) * u with the hardware exp2 and reciprocal (each within 1 ulp;
+                // the result is rounded to bf16 right after)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    float e = __builtin_amdgcn_exp2f(v[t] * -1.4426950408889634f);
+                    v[t] = v[t] * __builtin_amdgcn_rcpf(1.0f + e) * acc[i][j + FN / 2][t];
+                }
+            }
+            if (vec_ok && (INSIDE || gn < N)) {
+                if constexpr (TO_F32) {
+                    f32x4_t* dst = reinterpret_cast<f32x4_t*>(Cf + o);
+                    if constexpr (EPI == EPI_ADD_F32) {
+                        const f32x4_t old = *dst;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) v[t] += old[t];
+                    }
+                    *dst = v;
+                } else {
+                    uint2 pk;
+                    pk.x = pack_bf16x2(v[0], v[1]);
+                    pk.y = pack_bf16x2(v[2], v[3]);
+                    *reinterpret_cast<uint2*>(Dt + o) = pk;
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (gn + t < N) {
+                        if constexpr (EPI == EPI_ADD_F32) Cf[o + t] += v[t];
+                        else if constexpr (TO_F32) Cf[o + t] = v[t];
+                        else Dt[o + t].x = f32_to_bf16_bits(v[t]);
+                    }
+            }
+        }
+    }
 }
 
 // BM x BN block tile by NWM x NWN wavefronts; SA (SB) K-steps of A (B) in LDS.
@@ -146,16 +202,22 @@ gemm_mfma_body(char* smem, const bf16* __restrict__ A, const bf16* __restrict__ 
 #pragma unroll
         for (int j = 0; j < LB1; ++j) vb[j] = min(ld_row + j * NW * 8, rows_b - 1) * row_b + ld_col;
     }
+    // K need not be whole steps (big tile: it is): in the last one the lanes whose chunk lies past
+    // the row's end ask for an offset outside the buffer, which reads as zero.
+    const int nk = (K + BK - 1) / BK, last = !BIG && K % BK ? nk - 1 : -1;
+    const unsigned past = (int)ld_col >= (K % BK) * 2 ? PAST_THE_END : 0u;
     // load j of the wavefront's LA (LB) loads of a step's A (B) rows
     auto dma_a = [&](int kt, int stage, int j) {
         const unsigned k_b = (unsigned)kt * ROW_BYTES;
-        load_to_lds(rs_a, va[BIG ? 0 : j], BIG ? k_b + j * (NW * 8) * row_b : k_b,
+        const unsigned v = va[BIG ? 0 : j];
+        load_to_lds(rs_a, !BIG && kt == last ? v | past : v, BIG ? k_b + j * (NW * 8) * row_b : k_b,
                     lds0 + stage * A_TILE + j * (NW * 1024));
     };
     auto dma_b = [&](int kt, int stage, int j) {
         const unsigned k_b = (unsigned)kt * ROW_BYTES;
         const int jr = SILU ? j % LB1 : j;
-        load_to_lds(SILU && j >= LB1 ? rs_b2 : rs_b, vb[BIG ? 0 : jr], BIG ? k_b + jr * (NW * 8) * row_b : k_b,
+        const unsigned v = vb[BIG ? 0 : jr];
+        load_to_lds(SILU && j >= LB1 ? rs_b2 : rs_b, !BIG && kt == last ? v | past : v, BIG ? k_b + jr * (NW * 8) * row_b : k_b,
                     lds0 + A_ALL + stage * B_TILE + j * (NW * 1024));
     };
 
@@ -201,7 +263,6 @@ gemm_mfma_body(char* smem, const bf16* __restrict__ A, const bf16* __restrict__ 
     // registers): one barrier says so, and that step t + 1 has landed; the stages are then refilled
     // with steps t + SA and t + SB.  Of an operand with a stage more the loads go last and stay in
     // flight over a second barrier.
-    const int nk = K / BK;
     constexpr int LOADS = LA + LB, LEFT = (S - 2) * LOADS + XA * LA + XB * LB;
 #pragma unroll
     for (int t = 0; t < SA || t < SB; ++t)
@@ -347,54 +408,7 @@ gemm_mfma_body(char* smem, const bf16* __restrict__ A, const bf16* __restrict__ 
         }
 #undef CF_LOAD_ANGLES
     } else {
-        constexpr bool TO_F32 = (EPI == EPI_STORE_F32 || EPI == EPI_ADD_F32);
-        const bool vec_ok = (N & 3) == 0;             // row starts stay vector-aligned
-        constexpr int FN_OUT = SILU ? FN / 2 : FN;
-        constexpr int WN_OUT = SILU ? WN / 2 : WN;
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const int gm = m0 + wm * WM + i * 16 + frow;
-            if (!BIG && gm >= M) continue;
-#pragma unroll
-            for (int j = 0; j < FN_OUT; ++j) {
-                const int gn = n0 + wn * WN_OUT + j * 16 + 4 * fq;
-                const int64_t o = (int64_t)gm * N + gn;
-                f32x4_t v = acc[i][j];
-                if constexpr (SILU) {
-                    // silu(g) * u with the hardware exp2 and reciprocal (each within 1 ulp;
-                    // the result is rounded to bf16 right after)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        float e = __builtin_amdgcn_exp2f(v[t] * -1.4426950408889634f);
-                        v[t] = v[t] * __builtin_amdgcn_rcpf(1.0f + e) * acc[i][j + FN / 2][t];
-                    }
-                }
-                if (vec_ok && (BIG || gn < N)) {
-                    if constexpr (TO_F32) {
-                        f32x4_t* dst = reinterpret_cast<f32x4_t*>(Cf + o);
-                        if constexpr (EPI == EPI_ADD_F32) {
-                            const f32x4_t old = *dst;
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) v[t] += old[t];
-                        }
-                        *dst = v;
-                    } else {
-                        uint2 pk;
-                        pk.x = pack_bf16x2(v[0], v[1]);
-                        pk.y = pack_bf16x2(v[2], v[3]);
-                        *reinterpret_cast<uint2*>(Dt + o) = pk;
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        if (gn + t < N) {
-                            if constexpr (EPI == EPI_ADD_F32) Cf[o + t] += v[t];
-                            else if constexpr (TO_F32) Cf[o + t] = v[t];
-                            else Dt[o + t].x = f32_to_bf16_bits(v[t]);
-                        }
-                }
-            }
-        }
+        store_tile<EPI, FM, FN, BIG>(acc, Cf, Dt, M, N, m0 + wm * WM + frow, n0 + wn * (SILU ? WN / 2 : WN) + 4 * fq);
     }
 }
 
@@ -443,6 +457,92 @@ gemm_mfma_tail_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                tail_tiles_m * tail_tiles_n, none);
 }
 
+// Few rows: every row of A in one tile (BM >= M), BN columns per workgroup, so that the weights are
+// read once and by as many workgroups as N gives.  Bound by memory: what counts is the bytes in
+// flight and the serial chain of a workgroup's K-steps, so a stage of the ring holds G K-steps behind
+// ONE barrier, all of a stage's fragments are read into registers at once, and S stages are in flight.
+// The K order of an output element is that of every other tile.
+template <int EPI, int BM, int BN, int G, int S>
+__global__ void __launch_bounds__(BM == 16 ? 128 : 256)
+gemm_rows_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W, float* __restrict__ Cf,
+                 bf16* __restrict__ Dt, int M, int N, int K) {
+    extern __shared__ __align__(16) char smem[];
+    constexpr int NWM = BM == 16 ? 1 : 2, NWN = 2, NW = NWM * NWN;
+    constexpr int FM = BM / NWM / 16, FN = BN / NWN / 16;
+    constexpr int A_TILE = BM * ROW_BYTES, STEP_BYTES = (BM + BN) * ROW_BYTES, STAGE_BYTES = G * STEP_BYTES;
+    constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, LOADS = G * (LA + LB);
+    static_assert(LA * 8 * NW == BM && LB * 8 * NW == BN && EPI != EPI_SILU_MUL, "loader shape");
+    static_assert((S - 1) * LOADS <= 63, "the counter of loads in flight has six bits");
+    const int n0 = blockIdx.x * BN;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / NWN, wn = wave % NWN;
+    const unsigned row_b = (unsigned)K * 2u;
+    const int rows_a = M, rows_b = min(BN, N - n0);
+    const u32x4_t rs_a = buffer_rsrc(A, rows_a * row_b);
+    const u32x4_t rs_b = buffer_rsrc(W + (int64_t)n0 * K, rows_b * row_b);
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_ptr_t)smem + (unsigned)wave * 1024u);
+    const int ld_row = wave * 8 + (lane >> 3);
+    const unsigned ld_col = ((lane & 7) ^ swz(ld_row)) << 4;
+    unsigned va[LA], vb[LB];
+#pragma unroll
+    for (int j = 0; j < LA; ++j) va[j] = min(ld_row + j * NW * 8, rows_a - 1) * row_b + ld_col;
+#pragma unroll
+    for (int j = 0; j < LB; ++j) vb[j] = min(ld_row + j * NW * 8, rows_b - 1) * row_b + ld_col;
+    const int nk = (K + BK - 1) / BK, ns = (nk + G - 1) / G;
+    const int last = K % BK ? nk - 1 : -1;        // a partial step, see gemm_mfma_body
+    const unsigned past = (int)ld_col >= (K % BK) * 2 ? PAST_THE_END : 0u;
+    auto refill = [&](int t, int stage) {         // steps past the end fetch the last one again, unused
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int step = min(t * G + g, nk - 1);
+            const unsigned k_b = (unsigned)step * ROW_BYTES, at = lds0 + stage * STAGE_BYTES + g * STEP_BYTES;
+#pragma unroll
+            for (int j = 0; j < LA; ++j) load_to_lds(rs_a, step == last ? va[j] | past : va[j], k_b, at + j * (NW * 1024));
+#pragma unroll
+            for (int j = 0; j < LB; ++j) load_to_lds(rs_b, step == last ? vb[j] | past : vb[j], k_b, at + A_TILE + j * (NW * 1024));
+        }
+    };
+    const int frow = lane & 15, fq = lane >> 4, fswz = swz(frow);
+    f32x4_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    u32x4_t fa[2 * G][FM], fb[2 * G][FN];
+#pragma unroll
+    for (int t = 0; t < S; ++t) refill(t, t);
+    wait_barrier<(S - 1) * LOADS>();
+    int cur = 0;
+    for (int t = 0; t < ns; ++t) {
+        const char* st = smem + cur * STAGE_BYTES + frow * ROW_BYTES;
+#pragma unroll
+        for (int kk = 0; kk < 2 * G; ++kk) {
+            const int at = (kk >> 1) * STEP_BYTES + (((4 * (kk & 1) + fq) ^ fswz) << 4);
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+                fa[kk][i] = *reinterpret_cast<const u32x4_t*>(st + at + (wm * FM + i) * 16 * ROW_BYTES);
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                fb[kk][j] = *reinterpret_cast<const u32x4_t*>(st + at + A_TILE + (wn * FN + j) * 16 * ROW_BYTES);
+        }
+        wait_barrier<(S - 2) * LOADS>();          // stage read by all, the next one landed
+        refill(t + S, cur);
+#pragma unroll
+        for (int kk = 0; kk < 2 * G; ++kk)
+            if (t * G + (kk >> 1) < nk)           // the same for the whole launch
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[kk][j]),
+                                                                            __builtin_bit_cast(bf16x8_t, fa[kk][i]), acc[i][j], 0, 0, 0);
+        cur = cur + 1 == S ? 0 : cur + 1;
+    }
+    // the refills past the end must not land after the workgroup's LDS is given away
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    store_tile<EPI, FM, FN, false>(acc, Cf, Dt, M, N, wm * FM * 16 + frow, n0 + wn * (BN / NWN) + 4 * fq);
+}
+
 constexpr int N_CUS = 256;            // MI355X
 constexpr int GROUP_M = 8;            // tile rows per group of the tile order (see the body)
 
@@ -483,8 +583,20 @@ void launch_tile(hipStream_t s, const void* A, const void* W, const void* W2, fl
                                              (bf16*)Dt, M, N, K, tiles_m, tiles_n, rope);
 }
 
+template <int EPI, int BM, int BN, int G, int S>
+void launch_rows(hipStream_t s, const void* A, const void* W, float* Cf, void* Dt, int M, int N, int K) {
+    constexpr int LDS = S * G * (BM + BN) * ROW_BYTES;
+    static bool configured = false;
+    auto kern = gemm_rows_kernel<EPI, BM, BN, G, S>;
+    if (!configured) {
+        (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        configured = true;
+    }
+    kern<<<(N + BN - 1) / BN, BM == 16 ? 128 : 256, LDS, s>>>((const bf16*)A, (const bf16*)W, Cf, (bf16*)Dt, M, N, K);
+}
+
 int g_force_tile = 0;   // 0 = heuristic; 256 / 128 / 64 = forced tile, 257 = 256 with the quartered tail
-int g_small_below = 160;   // 64x64 tiles when there are fewer 128x128 tiles than this
+constexpr int ROWS_MAX_WG = 1024;     // workgroups of 32 columns up to which the few-row kernel is used
 
 template <int EPI>
 void launch(hipStream_t s, const void* A, const void* W, const void* W2, float* Cf, void* Dt, int M,
@@ -497,15 +609,25 @@ void launch(hipStream_t s, const void* A, const void* W, const void* W2, float* 
     bool big = (g_force_tile ? g_force_tile >= 256 : tiles256 >= need) && K % (2 * BK) == 0 &&
                M >= 256 && N >= BN_OUT256 && EPI != EPI_ADD_F32;
     if (big) { launch_tile<EPI, 256>(s, A, W, W2, Cf, Dt, M, N, K, g_force_tile == 0 || g_force_tile == 257); return; }
-    if constexpr (EPI != EPI_SILU_MUL) {
-        // few rows against a narrow weight (a tensor-parallel shard's QKV projection): 128x128
-        // tiles would leave most CUs idle, so quarter the tile.  The K order of every output
-        // element is the same for all tile shapes, so the result bits do not depend on the choice.
-        int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
-        bool small = g_force_tile ? g_force_tile == 64 : tiles128 < g_small_below;
-        if (small) { launch_tile<EPI, 64>(s, A, W, W2, Cf, Dt, M, N, K); return; }
-    }
-    launch_tile<EPI, 128>(s, A, W, W2, Cf, Dt, M, N, K);
+    // At most 32 rows: the few-row kernel, unless the weight is so wide (an LM head) that larger
+    // column tiles fill the chip anyway (us, 64x64 tiles against it -- N 4096, K 14336, 16 rows: 42,
+    // 23; N 1280, K 8192: 25, 14; N 6144, K 4096, 23 rows: 14, 10; N 128256: 188 with 128x128
+    // tiles against 205).  The gate/up pair has twice the columns and does better on the 64 tile.
+    if constexpr (EPI != EPI_SILU_MUL)
+        if (g_force_tile == 0 && M <= 32 && N <= 32 * ROWS_MAX_WG) {
+            if (M <= 16) launch_rows<EPI, 16, 32, 4, 3>(s, A, W, Cf, Dt, M, N, K);
+            else launch_rows<EPI, 32, 32, 4, 3>(s, A, W, Cf, Dt, M, N, K);
+            return;
+        }
+    // Fewer 128x128 tiles than CUs: quarter the tile (us, 128 against 64 tile -- gate/up 100 rows of
+    // 4096: 52, 45; 300 rows of 8192 x 3584: 67, 64; down 700 rows: 131, 121; above it the large tile
+    // wins: QKV 700 rows 44, 57).  The K order of every output element is the same for all tile
+    // shapes, so the result bits do not depend on the choice.
+    constexpr int BN_OUT128 = EPI == EPI_SILU_MUL ? 64 : 128;
+    const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + BN_OUT128 - 1) / BN_OUT128);
+    const bool small = g_force_tile ? g_force_tile == 64 : tiles128 < N_CUS;
+    if (small) launch_tile<EPI, 64>(s, A, W, W2, Cf, Dt, M, N, K);
+    else launch_tile<EPI, 128>(s, A, W, W2, Cf, Dt, M, N, K);
 }
 
 }  // namespace
@@ -532,6 +654,10 @@ void launch_gemm_mfma_qkv_rope(hipStream_t s, const void* A, const void* Wqkv, v
 bool gemm_mfma_supported(int dtype, int M, int N, int K, int epi) {
     (void)epi;
     return dtype == CF_BF16 && M > 0 && N > 0 && K >= BK && K % BK == 0;
+}
+
+bool gemm_mfma_takes(int dtype, int M, int N, int K) {
+    return dtype == CF_BF16 && M > 0 && N > 0 && K >= BK && K % 8 == 0 && K < (1 << 22);
 }
 
 bool gemm_mfma_aligned(const void* A, const void* W, const void* W2) {

@@ -114,6 +114,42 @@ def test_gemm_bits_do_not_depend_on_the_tile_shape(sess, mnk):
     assert torch.equal(outs[0][lo:], Cs)
 
 
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 65])
+@pytest.mark.parametrize("nk", [(96, 64), (130, 192), (1000, 1408), (64, 72), (33, 688), (2000, 712)])
+def test_gemm_few_rows_and_ragged_k(sess, rows, nk):
+    """Row counts at the edges of the few-row kernel, K of one step, of ragged groups of steps and
+    ending inside a step (72, 688, 712: whole 16-byte vectors).  The rows must come out with the bits
+    that they get inside a taller launch; 2^-24 per term against float64; the operands are followed by
+    NaN, which a read past a row's end would let in."""
+    import paper_2604_25080_amd as cf
+    N, K = nk
+    M = 700
+    g = torch.Generator().manual_seed(rows * 7 + N + K)
+    a, w, w2 = (torch.full((r * K + 64,), float("nan")).bfloat16() for r in (M, N, N))
+    for t, r, std in ((a, M, 1.0), (w, N, 0.05), (w2, N, 0.05)):
+        t[:r * K] = (torch.randn(r * K, generator=g) * std).bfloat16()
+    A, W, W2 = a.cuda(), w.cuda(), w2.cuda()
+    few = a.clone()
+    few[rows * K:] = float("nan")
+    Few = few.cuda()
+    x, y, y2 = a[:rows * K].view(rows, K).double(), w[:N * K].view(N, K).double(), w2[:N * K].view(N, K).double()
+    ref, ref2 = x @ y.t(), x @ y2.t()
+    for epi in (cf.EPI_STORE_F32, cf.EPI_STORE_T, cf.EPI_SILU_MUL):
+        dt = torch.float32 if epi == cf.EPI_STORE_F32 else torch.bfloat16
+        out, tall = torch.zeros(rows, N, dtype=dt, device="cuda"), torch.zeros(M, N, dtype=dt, device="cuda")
+        for src, dst, m in ((Few, out, rows), (A, tall, M)):
+            p = dst.data_ptr()
+            sess.ctx.op_gemm(src.data_ptr(), W.data_ptr(), W2.data_ptr(), p if dt == torch.float32 else 0,
+                             0 if dt == torch.float32 else p, m, N, K, epi, 0)
+        assert torch.equal(out, tall[:rows])
+        if epi == cf.EPI_STORE_F32:
+            err, bound = (out.cpu().double() - ref).abs(), K * 2.0 ** -24 * (x.abs() @ y.abs().t())
+        else:
+            r = ref if epi == cf.EPI_STORE_T else ref * torch.sigmoid(ref) * ref2
+            err, bound = (out.cpu().double() - r).abs(), 2.0 ** -8 * r.abs() + 1e-5
+        assert bool((err <= bound).all())
+
+
 @pytest.mark.parametrize("at_a, at_w", [(2, 0), (0, 6), (1, 0), (0, 3)])
 def test_gemm_operands_that_start_inside_a_larger_buffer(sess, at_a, at_w):
     """Whole-dword starts take the matrix-core kernel, odd elements the plain one; 2^-24 per term."""
