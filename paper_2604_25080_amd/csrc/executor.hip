@@ -653,26 +653,30 @@ int run_phase(cf_ctx* c, cf_cache* cache, const Phase& ph, int n_layers_max,
             int rec_end = std::min(ci.r_mid, Ta_rec), rec_cont = std::min(ci.r_mid, Tn_rec);
             bool has_rec = rec_end > ci.r0, has_new = ci.r1 > ci.r_mid;
             if (!has_rec && !has_new) continue;
-            // row ranges of this chunk in this layer: {x, y (rows needing K/V), ycont (rows going on)}
-            int ranges[2][3], n_ranges = 0;
-            if (has_rec && has_new && rec_cont == ci.r_mid) {
-                ranges[n_ranges][0] = ci.r0; ranges[n_ranges][1] = ci.r1; ranges[n_ranges][2] = ci.r1; ++n_ranges;
+            // The norm and the K/V projection run over all rows of the chunk that are active, in one go
+            // where they are adjacent (recompute rows ending with this layer included); what follows
+            // them runs over the rows that go on, which are adjacent only if no recompute row ends here.
+            int kv[2][2], n_kv = 0, ranges[2][2], n_ranges = 0;
+            if (has_rec && has_new && rec_end == ci.r_mid) {
+                kv[n_kv][0] = ci.r0; kv[n_kv++][1] = ci.r1;
             } else {
-                if (has_rec) { ranges[n_ranges][0] = ci.r0; ranges[n_ranges][1] = rec_end; ranges[n_ranges][2] = std::max(rec_cont, ci.r0); ++n_ranges; }
-                if (has_new) { ranges[n_ranges][0] = ci.r_mid; ranges[n_ranges][1] = ci.r1; ranges[n_ranges][2] = ci.r1; ++n_ranges; }
+                if (has_rec) { kv[n_kv][0] = ci.r0; kv[n_kv++][1] = rec_end; }
+                if (has_new) { kv[n_kv][0] = ci.r_mid; kv[n_kv++][1] = ci.r1; }
             }
-            for (int ri = 0; ri < n_ranges; ++ri) {
-                const int x = ranges[ri][0], y = ranges[ri][1], ycont = ranges[ri][2];
-                const int Tc = y - x, Tr = ycont - x, xo = x - ci.r0;   // xo: row offset inside the chunk buffers
-                float* h = h_rows + (size_t)x * d;
-                float* dl = dl_rows + (size_t)x * d;
+            if (has_new && rec_cont == ci.r_mid) {
+                ranges[n_ranges][0] = ci.r0; ranges[n_ranges++][1] = ci.r1;
+            } else {
+                if (rec_cont > ci.r0) { ranges[n_ranges][0] = ci.r0; ranges[n_ranges++][1] = rec_cont; }
+                if (has_new) { ranges[n_ranges][0] = ci.r_mid; ranges[n_ranges++][1] = ci.r1; }
+            }
+            for (int ki = 0; ki < n_kv; ++ki) {
+                const int x = kv[ki][0], Tc = kv[ki][1] - x, xo = x - ci.r0;   // xo: row offset inside the chunk buffers
                 char* a_buf = (char*)c->a() + (size_t)xo * d * es;
                 float* qkv_buf = c->qkv() + (size_t)xo * qcols;
                 char* q_buf = (char*)c->q() + (size_t)xo * nq * es;
-                char* o_buf = (char*)c->o() + (size_t)xo * nq * es;
-                char* act_buf = (char*)c->act() + (size_t)xo * m.d_ffn * es;
                 c->prof_begin(CF_K_RMSNORM, (double)Tc * d * (4 + es), c->cs);
-                launch_rmsnorm(c->cs, m.dtype, h, l > 0 ? dl : nullptr, lw.attn_norm, a_buf, Tc, d, m.rms_eps, nullptr);
+                launch_rmsnorm(c->cs, m.dtype, h_rows + (size_t)x * d, l > 0 ? dl_rows + (size_t)x * d : nullptr,
+                               lw.attn_norm, a_buf, Tc, d, m.rms_eps, nullptr);
                 c->prof_end(CF_K_RMSNORM, c->cs);
                 if (!c->simple_only && gemm_mfma_qkv_rope_supported(m.dtype, Tc, qcols, d, m.head_dim) &&
                     gemm_mfma_aligned(a_buf, lw.wqkv, nullptr)) {
@@ -688,7 +692,15 @@ int run_phase(cf_ctx* c, cf_cache* cache, const Phase& ph, int n_layers_max,
                                       Tc, m.n_q_heads, g);
                     c->prof_end(CF_K_ROPE_WRITE, c->cs);
                 }
-                if (Tr <= 0) continue;
+            }
+            for (int ri = 0; ri < n_ranges; ++ri) {
+                const int x = ranges[ri][0], ycont = ranges[ri][1];
+                const int Tr = ycont - x, xo = x - ci.r0;
+                float* h = h_rows + (size_t)x * d;
+                float* dl = dl_rows + (size_t)x * d;
+                char* a_buf = (char*)c->a() + (size_t)xo * d * es;
+                char* o_buf = (char*)c->o() + (size_t)xo * nq * es;
+                char* act_buf = (char*)c->act() + (size_t)xo * m.d_ffn * es;
                 // attention work items (row0 is relative to the chunk): recompute items lead, new-turn
                 // items trail.  Recompute rows run first; the new-turn rows also read this layer's
                 // loaded KV and therefore wait for the copy stream to have delivered it.
@@ -1346,11 +1358,8 @@ extern "C" int cf_restore_batch(cf_ctx* c, cf_cache* cache, int32_t B, const cf_
     if (logits_out) {
         // first-token logits; the last layer's down-proj result is still pending in dl
         launch_rmsnorm(c->cs, m.dtype, c->h(), c->dl(), c->w.final_norm, c->a_last(), B, m.d_model,
-                       m.rms_eps, (const int32_t*)(md + off_last));
+                       m.rms_eps, (const int32_t*)(md + off_last), c->h_last());   // kept for cf_read_final_hidden
         gemm(c, CF_K_GEMM_LM_HEAD, c->a_last(), c->w.lm_head, nullptr, logits_out, nullptr, B, m.vocab, m.d_model, EPI_STORE_F32);
-        // the rows the head saw, kept for cf_read_final_hidden
-        launch_residual_gather(c->cs, c->h_last(), c->h(), c->dl(), (const int32_t*)(md + off_last), B, m.d_model,
-                               0, INT32_MAX, 0, 0);
         c->n_last = B;
     }
     CF_HIP_Q(hipStreamWaitEvent(c->cs, c->ev_copy, 0));
@@ -2049,10 +2058,8 @@ extern "C" int cf_restore_dynamic(cf_ctx* c, cf_cache* cache, int32_t B, const c
             launch_rmsnorm(c->cs, m.dtype, c->h() + (size_t)lw.T * m.d_model,
                            c->dl() + (size_t)lw.T * m.d_model, c->w.final_norm,
                            (char*)c->a_last() + (size_t)i * m.d_model * es, 1, m.d_model, m.rms_eps,
-                           (const int32_t*)(md + off_idx) + k);
-            launch_residual_gather(c->cs, c->h_last() + (size_t)i * m.d_model, c->h() + (size_t)lw.T * m.d_model,
-                                   c->dl() + (size_t)lw.T * m.d_model, (const int32_t*)(md + off_idx) + k, 1,
-                                   m.d_model, 0, INT32_MAX, 0, 0);
+                           (const int32_t*)(md + off_idx) + k,
+                           c->h_last() + (size_t)i * m.d_model);
             prefilled[i] = 1;
             ++n_prefilled;
         }
@@ -2224,10 +2231,8 @@ extern "C" int cf_restore_dynamic(cf_ctx* c, cf_cache* cache, int32_t B, const c
                         launch_rmsnorm(c->cs, m.dtype, c->h() + (size_t)lw.T * m.d_model,
                                        c->dl() + (size_t)lw.T * m.d_model, c->w.final_norm,
                                        (char*)c->a_last() + (size_t)i * m.d_model * es, 1, m.d_model, m.rms_eps,
-                                       (const int32_t*)(md + off_idx) + k);
-                        launch_residual_gather(c->cs, c->h_last() + (size_t)i * m.d_model,
-                                               c->h() + (size_t)lw.T * m.d_model, c->dl() + (size_t)lw.T * m.d_model,
-                                               (const int32_t*)(md + off_idx) + k, 1, m.d_model, 0, INT32_MAX, 0, 0);
+                                       (const int32_t*)(md + off_idx) + k,
+                           c->h_last() + (size_t)i * m.d_model);
                         prefilled[i] = 1;
                         ++n_prefilled;
                     }

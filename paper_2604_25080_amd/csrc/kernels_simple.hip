@@ -49,7 +49,7 @@ template <typename T, int NV>
 __global__ void __launch_bounds__(256)
 rmsnorm_kernel(float* __restrict__ h, const float* __restrict__ delta,
                const float* __restrict__ gain, T* __restrict__ out, int d, float eps,
-               const int32_t* __restrict__ row_idx) {
+               const int32_t* __restrict__ row_idx, float* __restrict__ sum_out) {
     __shared__ float red[4];
     int t = blockIdx.x;
     int64_t srow = row_idx ? row_idx[t] : t;
@@ -99,6 +99,7 @@ rmsnorm_kernel(float* __restrict__ h, const float* __restrict__ delta,
     for (int i = 0; i < MAXV; ++i) {
         int idx = threadIdx.x + i * 256;
         if (idx < nvec) {
+            if (sum_out) reinterpret_cast<float4*>(sum_out + (int64_t)t * d)[idx] = v[i];
             float4 g = reinterpret_cast<const float4*>(gain)[idx];
             dst[idx * 4 + 0] = from_f32<T>(v[i].x * r * g.x);
             dst[idx * 4 + 1] = from_f32<T>(v[i].y * r * g.y);
@@ -109,16 +110,16 @@ rmsnorm_kernel(float* __restrict__ h, const float* __restrict__ delta,
 }
 
 void launch_rmsnorm(hipStream_t s, int dtype, float* h, const float* delta, const float* gain,
-                    void* out, int T, int d, float eps, const int32_t* row_idx) {
+                    void* out, int T, int d, float eps, const int32_t* row_idx, float* sum_out) {
     if (T <= 0) return;
     if (dtype == CF_F32)
-        rmsnorm_kernel<float, 0><<<T, 256, 0, s>>>(h, delta, gain, (float*)out, d, eps, row_idx);
+        rmsnorm_kernel<float, 0><<<T, 256, 0, s>>>(h, delta, gain, (float*)out, d, eps, row_idx, sum_out);
     else if (d == 4096)
-        rmsnorm_kernel<bf16, 4><<<T, 256, 0, s>>>(h, delta, gain, (bf16*)out, d, eps, row_idx);
+        rmsnorm_kernel<bf16, 4><<<T, 256, 0, s>>>(h, delta, gain, (bf16*)out, d, eps, row_idx, sum_out);
     else if (d == 8192)
-        rmsnorm_kernel<bf16, 8><<<T, 256, 0, s>>>(h, delta, gain, (bf16*)out, d, eps, row_idx);
+        rmsnorm_kernel<bf16, 8><<<T, 256, 0, s>>>(h, delta, gain, (bf16*)out, d, eps, row_idx, sum_out);
     else
-        rmsnorm_kernel<bf16, 0><<<T, 256, 0, s>>>(h, delta, gain, (bf16*)out, d, eps, row_idx);
+        rmsnorm_kernel<bf16, 0><<<T, 256, 0, s>>>(h, delta, gain, (bf16*)out, d, eps, row_idx, sum_out);
 }
 
 // ---------------------------------------------------------------- simple GEMM
