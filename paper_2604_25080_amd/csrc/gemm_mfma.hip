@@ -598,16 +598,19 @@ void launch_rows(hipStream_t s, const void* A, const void* W, float* Cf, void* D
 int g_force_tile = 0;   // 0 = heuristic; 256 / 128 / 64 = forced tile, 257 = 256 with the quartered tail
 constexpr int ROWS_MAX_WG = 1024;     // workgroups of 32 columns up to which the few-row kernel is used
 
+// The big tile once 128x128 tiles would take more than one round (two workgroups per CU): a round of
+// big tiles, however empty, costs 1.6 of theirs (us at N 4096, K 4096 -- 2048 rows, 512 tiles: 58 against
+// 77; 2560 rows, 640 tiles: 93 against 77; K 14336, 2560 rows: 325 against 243).
+inline bool prefer_big(int M, int N, int bn_out128) {
+    return (int64_t)((M + 127) / 128) * ((N + bn_out128 - 1) / bn_out128) > 2 * N_CUS;
+}
+
 template <int EPI>
 void launch(hipStream_t s, const void* A, const void* W, const void* W2, float* Cf, void* Dt, int M,
             int N, int K) {
-    constexpr int BN_OUT256 = (EPI == EPI_SILU_MUL) ? 128 : 256;
-    int64_t tiles256 = (int64_t)((M + 255) / 256) * ((N + BN_OUT256 - 1) / BN_OUT256);
-    // big tiles once there is at least one per CU (thresholds measured per epilogue); the
-    // read-modify-write epilogue always takes the small tile (two blocks per CU overlap it)
-    int64_t need = EPI == EPI_SILU_MUL ? 200 : 256;
-    bool big = (g_force_tile ? g_force_tile >= 256 : tiles256 >= need) && K % (2 * BK) == 0 &&
-               M >= 256 && N >= BN_OUT256 && EPI != EPI_ADD_F32;
+    constexpr int BN_OUT128 = EPI == EPI_SILU_MUL ? 64 : 128;
+    const bool big = (g_force_tile ? g_force_tile >= 256 : prefer_big(M, N, BN_OUT128)) && K % (2 * BK) == 0 &&
+                     M >= 256 && N >= 2 * BN_OUT128 && EPI != EPI_ADD_F32;
     if (big) { launch_tile<EPI, 256>(s, A, W, W2, Cf, Dt, M, N, K, g_force_tile == 0 || g_force_tile == 257); return; }
     // At most 32 rows: the few-row kernel, unless the weight is so wide (an LM head) that larger
     // column tiles fill the chip anyway (us, 64x64 tiles against it -- N 4096, K 14336, 16 rows: 42,
@@ -619,13 +622,13 @@ void launch(hipStream_t s, const void* A, const void* W, const void* W2, float* 
             else launch_rows<EPI, 32, 32, 4, 3>(s, A, W, Cf, Dt, M, N, K);
             return;
         }
-    // Fewer 128x128 tiles than CUs: quarter the tile (us, 128 against 64 tile -- gate/up 100 rows of
-    // 4096: 52, 45; 300 rows of 8192 x 3584: 67, 64; down 700 rows: 131, 121; above it the large tile
-    // wins: QKV 700 rows 44, 57).  The K order of every output element is the same for all tile
-    // shapes, so the result bits do not depend on the choice.
-    constexpr int BN_OUT128 = EPI == EPI_SILU_MUL ? 64 : 128;
-    const int64_t tiles128 = (int64_t)((M + 127) / 128) * ((N + BN_OUT128 - 1) / BN_OUT128);
-    const bool small = g_force_tile ? g_force_tile == 64 : tiles128 < N_CUS;
+    // One and a half rounds of 64x64 tiles (two workgroups per CU) or fewer: quarter the tile (us, 128
+    // against 64 tile -- gate/up 100 rows of 4096: 52, 45; 300 rows of 8192 x 3584: 67, 64; down 700 rows:
+    // 131, 121; N 1280, K 8192 2048 rows: 70, 66; above it the large tile wins: 3072 of those rows 76,
+    // 89).  The K order of every output element is the same for all tile shapes, so the result bits do
+    // not depend on the choice.
+    const int64_t tiles64 = (int64_t)((M + 63) / 64) * ((N + BN_OUT128 / 2 - 1) / (BN_OUT128 / 2));
+    const bool small = g_force_tile ? g_force_tile == 64 : tiles64 <= 3 * N_CUS;
     if (small) launch_tile<EPI, 64>(s, A, W, W2, Cf, Dt, M, N, K);
     else launch_tile<EPI, 128>(s, A, W, W2, Cf, Dt, M, N, K);
 }
@@ -637,8 +640,7 @@ void gemm_mfma_force_tile(int t) { g_force_tile = t; }
 bool gemm_mfma_qkv_rope_supported(int dtype, int M, int N, int K, int head_dim) {
     // the shapes for which the float-output QKV GEMM would take the big tile anyway, with whole
     // tiles along N (no shifted edge tile: head boundaries stay on wave-tile boundaries)
-    const int64_t tiles256 = (int64_t)((M + 255) / 256) * (N / 256);
-    const bool big = g_force_tile ? g_force_tile >= 256 : tiles256 >= 256;
+    const bool big = g_force_tile ? g_force_tile >= 256 : prefer_big(M, N, 128);
     return dtype == CF_BF16 && (head_dim == 128 || head_dim == 64) && big && M >= 256 && N >= 256 &&
            N % 256 == 0 && K >= 2 * BK && K % (2 * BK) == 0;
 }
