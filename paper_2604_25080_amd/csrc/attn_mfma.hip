@@ -78,9 +78,13 @@ attention_mfma_kernel(const bf16* __restrict__ q, bf16* __restrict__ out, float*
     const int item = blockIdx.x / n_blocks_h, hb = blockIdx.x % n_blocks_h;
     AttnWork w = work[gridDim.x / n_blocks_h - 1 - item];
     int tid = threadIdx.x, lane = tid & 63;
-    int wave = (tid >> 6) & 3;                     // which 32 query rows
-    // wavefronts 4-7 take the second head of the pair
-    int head = ((hb % n_kv_b) * per_kv + hb / n_kv_b) * HPB + (tid >> 8);
+    // Which 32 query rows; wavefronts 4-7 take the second head of the pair, two row blocks on: wavefronts w
+    // and w + 4 share a SIMD, and an item of up to 64 rows then has one wavefront at work on each. The index
+    // is uniform, so it is read into a scalar register and the causal tests below are scalar branches
+    // (40 960 rows: 943 -> 961 TF; a 70B rank's 16 000: 747 -> 758).
+    const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = (wave8 & 3) ^ (wave8 >> 2 << 1);
+    int head = ((hb % n_kv_b) * per_kv + hb / n_kv_b) * HPB + (wave8 >> 2);
     int gk = head / (n_q_heads / g.n_kv_heads);    // the same KV head for both (group size is even)
     const int32_t* pt = page_tables + w.pt_off;
     int lq = lane & 31, lh = lane >> 5;
@@ -91,6 +95,10 @@ attention_mfma_kernel(const bf16* __restrict__ q, bf16* __restrict__ out, float*
     int qpos = w.pos0 + row;
     int wave_last_q = w.pos0 + min(wave * 32 + 31, w.n_rows - 1);   // wave-uniform
     int wave_first_q = w.pos0 + min(wave * 32, w.n_rows - 1);
+    // In an item of fewer than 128 rows the wavefronts without rows only move tiles: the scores, the
+    // softmax and the products of a tile take turns on a SIMD, so a wavefront on padding costs the one it
+    // shares the SIMD with its time (64 new rows over 16 k and over 12 k keys: 103 -> 83 us a launch).
+    const bool active = wave * 32 < w.n_rows;
 
     // ---- Q fragments: B operand of S^T = K Q^T, lane = query row lq, 8 hd values per step
     u32x4_t qf[QK_STEPS];
@@ -195,7 +203,7 @@ attention_mfma_kernel(const bf16* __restrict__ q, bf16* __restrict__ out, float*
         char* cur = smem + ((tile - t0) & 1) * STAGE;
         char* nxt = smem + ((tile - t0 + 1) & 1) * STAGE;
         int key_base = tile * KT;
-        if (key_base <= wave_last_q) {               // wave-uniform: tile not fully masked
+        if (active && key_base <= wave_last_q) {     // wave-uniform: rows here, tile not fully masked
             // ---- S^T = K Q^T : two 32-key fragments
             f32x16_t s[2];
 #pragma unroll

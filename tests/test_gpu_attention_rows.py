@@ -1,5 +1,6 @@
 """New turns of small batches: the attention kernel for few query blocks over short contexts, at the
-edges of its 16- and 32-row blocks, its pages and its 32-key groups, against the oracle."""
+edges of its 16- and 32-row blocks, its pages and its 32-key groups; and, in the recomputed contexts, the
+kernel for everything else on items that leave some of its wavefronts without rows.  Against the oracle."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,10 @@ pytestmark = pytest.mark.gpu
     ("mini-bf16", [3, 129, 63] + [20] * 15, [33, 1, 16] + [2] * 15),                 # 32-row blocks
     ("mini64-gqa2-bf16", [47, 64, 1, 100], [1, 15, 33, 65]),
     ("mini128-gqa3-bf16", [32, 17, 96], [16, 5, 32]),
-    ("mini64-bf16", [16, 70], [48, 1])])
+    ("mini64-bf16", [16, 70], [48, 1]),
+    ("mini-bf16", [32, 33, 64, 65, 96, 97, 128], [1] * 7),                           # contexts: 1 to 4 wavefronts with rows
+    ("mini64-gqa2-bf16", [129, 161, 193, 225], [1] * 4),
+    ("mini128-gqa3-bf16", [97, 192], [1, 1])])
 def test_new_turn_rows_match_the_oracle(shape_name, n_ctx, n_new):
     """2e-2 on the logits and on the cells, the stated bound of the bf16 models.  The pool starts as NaN
     patterns, so a slot past a request's last key must not reach any result."""
