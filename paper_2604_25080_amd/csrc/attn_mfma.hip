@@ -574,11 +574,18 @@ void launch_attention_mfma(hipStream_t s, const void* q, void* out, float* part_
     }
 }
 
-// Fewer workgroups of the 128-row kernel than CUs, and no key range split (that takes contexts of 2048
-// tokens and more, where the 128-row kernel's slices fill the chip): above either line the larger block
-// reads K and V less often and wins.
-bool attention_rows_fits(int n_work, int n_groups, int n_q_heads, int n_kv_heads) {
-    return n_groups == 0 && (int64_t)n_work * (n_q_heads / attention_mfma_heads_per_block(n_q_heads, n_kv_heads)) < 256;
+// Fewer workgroups of the 128-row kernel than CUs, at most two 32-row blocks with rows per CU, and no key
+// range split (that takes contexts of 2048 tokens and more, where the 128-row kernel's slices fill the
+// chip): above any of these lines the larger block reads K and V less often and wins.  us for two layers,
+// 128-row kernel against this one -- 512 rows over 512 keys, 32 heads (512 blocks): 83, 72; 4 x 512 over
+// 1500, 8 heads (512): 150, 115; 6 x 256 over 300 to 800, 32 heads (1536): 102, 209; 1536 over 384
+// (1536): 147, 264.
+bool attention_rows_fits(const AttnWork* work, int n_work, int n_groups, int n_q_heads, int n_kv_heads) {
+    if (n_groups != 0 || (int64_t)n_work * (n_q_heads / attention_mfma_heads_per_block(n_q_heads, n_kv_heads)) >= 256)
+        return false;
+    int64_t blocks = 0;
+    for (int i = 0; i < n_work; ++i) blocks += (work[i].n_rows + 31) / 32 * n_q_heads;
+    return blocks <= 512;
 }
 
 void launch_attention_rows(hipStream_t s, const void* q, void* out, const void* pool_layer, const AttnWork* work,
