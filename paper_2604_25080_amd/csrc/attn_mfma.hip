@@ -28,7 +28,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
@@ -313,195 +312,6 @@ attention_mfma_kernel(const bf16* __restrict__ q, bf16* __restrict__ out, float*
     }
 }
 
-// Few query blocks over short contexts (the new turns of a small batch).  The kernel above would walk
-// such a launch with a handful of workgroups, each serially through its tiles, most of its wavefronts on
-// padding.  Here a workgroup takes 16 * NQ query rows of one head and its four wavefronts take the
-// 32-key groups (two pages) in turn, each with its own running maximum, sum and output, merged through
-// LDS at the end.  The wavefronts share no keys, so K and V fragments come straight from the pages into
-// registers, one group ahead.  The score fragments pick their keys so that a lane's eight probabilities
-// are eight consecutive keys: 16 bytes of a V^T row.  A row's result does not depend on NQ or on what
-// else is in the block (groups past its position add exact zeros).
-// Bound by the latency of a wavefront's chain of groups: 23 rows over 723 keys, 32 heads of 128:
-// 27 -> 15 us a launch; 4 items of 1 to 64 rows over 77 to 1502 keys, 8 heads: 45 -> 18.
-template <int HD, int NQ>
-__global__ void __launch_bounds__(256, 1)
-attention_rows_kernel(const bf16* __restrict__ q, bf16* __restrict__ out, const bf16* __restrict__ pool_layer,
-                      const AttnWork* __restrict__ work, const int32_t* __restrict__ page_tables, int n_q_heads,
-                      KvGeom g) {
-    constexpr int ROWS = 16 * NQ, SUB = ATTN_BLOCK_ROWS / ROWS, KK = HD / 32, NT = HD / 16, PAD = 20;
-    constexpr int GROUP_KEYS = 2 * CF_PAGE_TOKENS;
-    __shared__ __align__(16) float o_sh[4][ROWS][PAD];        // one 16-wide slice of head_dim at a time
-    __shared__ float m_sh[4][ROWS], l_sh[4][ROWS];
-    const int blk = gridDim.x - 1 - blockIdx.x;               // the longest items are listed last
-    const AttnWork w = work[blk / SUB];
-    const int r0 = blk % SUB * ROWS;
-    if (r0 >= w.n_rows) return;
-    const int head = blockIdx.y, gk = head / (n_q_heads / g.n_kv_heads);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int li = lane & 15, lg = lane >> 4;
-    const int32_t* pt = page_tables + w.pt_off;
-    const int n_keys = w.pos0 + min(r0 + ROWS, w.n_rows);     // keys the block's last row sees
-    const int n_groups = (n_keys + GROUP_KEYS - 1) / GROUP_KEYS, last_page = (n_keys - 1) / CF_PAGE_TOKENS;
-
-    u32x4_t qf[NQ][KK];
-    int qpos[NQ];
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-        const int row = min(r0 + 16 * n + li, w.n_rows - 1);  // padded rows repeat the last row
-        qpos[n] = w.pos0 + row;
-        const bf16* qrow = q + ((int64_t)(w.row0 + row) * n_q_heads + head) * HD;
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) qf[n][kk] = *reinterpret_cast<const u32x4_t*>(qrow + kk * 32 + lg * 8);
-    }
-    // score fragment f, row i: key 8 (i / 4) + 4 f + i % 4 of the group; V^T row li, keys 8 lg .. + 7
-    const int64_t k_off = (int64_t)gk * CF_PAGE_TOKENS * HD + (8 * ((li >> 2) & 1) + (li & 3)) * HD + lg * 8;
-    const int64_t v_off = (int64_t)g.n_kv_heads * CF_PAGE_TOKENS * HD + (int64_t)gk * HD * CF_PAGE_TOKENS +
-                          li * CF_PAGE_TOKENS + (lg & 1) * 8;
-    u32x4_t kf[2][KK], vf[NT], kn[2][KK], vn[NT];
-    auto fetch = [&](int grp, u32x4_t (&k)[2][KK], u32x4_t (&v)[NT]) {
-        const int p0 = pt[min(2 * grp, last_page)], p1 = pt[min(2 * grp + 1, last_page)];
-        const bf16* kp = pool_layer + (int64_t)(li >> 3 ? p1 : p0) * g.page_elems + k_off;
-        const bf16* vp = pool_layer + (int64_t)(lg >> 1 ? p1 : p0) * g.page_elems + v_off;
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) k[f][kk] = *reinterpret_cast<const u32x4_t*>(kp + f * 4 * HD + kk * 32);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) v[t] = *reinterpret_cast<const u32x4_t*>(vp + t * 16 * CF_PAGE_TOKENS);
-    };
-    f32x4_t o[NQ][NT];
-    float m_run[NQ], l_run[NQ];                               // running maximum (log2 domain), partial row sum
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-        m_run[n] = -INFINITY;
-        l_run[n] = 0.f;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) o[n][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-    const float scale_log2e = rsqrtf((float)HD) * 1.4426950408889634f;
-    fetch(wave, kf, vf);
-    for (int grp = wave; grp < n_groups; grp += 4) {
-        fetch(grp + 4, kn, vn);
-        const int key0 = grp * GROUP_KEYS + 8 * lg;           // score (f, r): key key0 + 4 f + r
-        if (grp == n_groups - 1) {
-            // slots past the last needed key may hold anything: zero them, 0 * NaN must not get in
-            const int left = n_keys - key0;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                u32x4_t& val = vf[t];
-                val.x = left <= 0 ? 0u : (left == 1 ? val.x & 0xFFFFu : val.x);
-                val.y = left <= 2 ? 0u : (left == 3 ? val.y & 0xFFFFu : val.y);
-                val.z = left <= 4 ? 0u : (left == 5 ? val.z & 0xFFFFu : val.z);
-                val.w = left <= 6 ? 0u : (left == 7 ? val.w & 0xFFFFu : val.w);
-            }
-        }
-        f32x4_t sc[2][NQ];
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-                for (int n = 0; n < NQ; ++n)
-                    sc[f][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8_t, kf[f][kk]), __builtin_bit_cast(bf16x8_t, qf[n][kk]),
-                        kk == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sc[f][n], 0, 0, 0);
-        u32x4_t pf[NQ];
-#pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-            float mx = -INFINITY;
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    sc[f][n][r] = key0 + 4 * f + r > qpos[n] ? -INFINITY : sc[f][n][r];
-                    mx = fmaxf(mx, sc[f][n][r]);
-                }
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m_run[n], mx * scale_log2e);
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;    // no visible key yet
-            const float corr = __builtin_amdgcn_exp2f(m_run[n] - m_use);
-            m_run[n] = m_new;
-            float psum = 0.f;
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    sc[f][n][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[f][n][r], scale_log2e, -m_use));
-                    psum += sc[f][n][r];
-                }
-            l_run[n] = l_run[n] * corr + psum;
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[n][t][r] *= corr;
-            pf[n].x = pack_bf16x2(sc[0][n][0], sc[0][n][1]);
-            pf[n].y = pack_bf16x2(sc[0][n][2], sc[0][n][3]);
-            pf[n].z = pack_bf16x2(sc[1][n][0], sc[1][n][1]);
-            pf[n].w = pack_bf16x2(sc[1][n][2], sc[1][n][3]);
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int n = 0; n < NQ; ++n)
-                o[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vf[t]),
-                                                                  __builtin_bit_cast(bf16x8_t, pf[n]), o[n][t], 0, 0, 0);
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) kf[f][kk] = kn[f][kk];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) vf[t] = vn[t];
-    }
-    // ---- merge the four wavefronts
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-        l_run[n] += __shfl_xor(l_run[n], 16);
-        l_run[n] += __shfl_xor(l_run[n], 32);
-        if (lg == 0) { m_sh[wave][16 * n + li] = m_run[n]; l_sh[wave][16 * n + li] = l_run[n]; }
-    }
-    __syncthreads();
-    float share[NQ];                                          // this wavefront's share of a row, normalised
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-        const int r = 16 * n + li;
-        float m = m_sh[0][r];                                 // wavefront 0 has group 0: finite for every row
-#pragma unroll
-        for (int v = 1; v < 4; ++v) m = fmaxf(m, m_sh[v][r]);
-        float l = 0.f;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) l += l_sh[v][r] * __builtin_amdgcn_exp2f(m_sh[v][r] - m);
-        share[n] = __builtin_amdgcn_exp2f(m_run[n] - m) / l;
-    }
-    // register r of tile t: head_dim 16 t + 4 lg + r of query row li
-    const int st_row = threadIdx.x >> 2, st_c = (threadIdx.x & 3) * 4;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-#pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-            f32x4_t x = o[n][t];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] *= share[n];
-            *reinterpret_cast<f32x4_t*>(&o_sh[wave][16 * n + li][4 * lg]) = x;
-        }
-        __syncthreads();
-        if (st_row < ROWS && r0 + st_row < w.n_rows) {
-            f32x4_t x = *reinterpret_cast<const f32x4_t*>(&o_sh[0][st_row][st_c]);
-#pragma unroll
-            for (int v = 1; v < 4; ++v) {
-                const f32x4_t y = *reinterpret_cast<const f32x4_t*>(&o_sh[v][st_row][st_c]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) x[r] += y[r];
-            }
-            u32x2_t val;
-            val.x = pack_bf16x2(x[0], x[1]);
-            val.y = pack_bf16x2(x[2], x[3]);
-            *reinterpret_cast<u32x2_t*>(out + ((int64_t)(w.row0 + r0 + st_row) * n_q_heads + head) * HD + 16 * t + st_c) = val;
-        }
-        __syncthreads();
-    }
-}
-
 // Merge the partial results of one (q-block, head): one wavefront per query row, four rows
 // per workgroup (blockIdx.z picks the row quad), so the merge is spread over thousands of
 // wavefronts instead of walking 32 rows per wavefront through dependent loads.
@@ -572,32 +382,6 @@ void launch_attention_mfma(hipStream_t s, const void* q, void* out, float* part_
         else
             attention_combine_kernel<64><<<cgrid, 256, 0, s>>>((bf16*)out, part_buf, groups, n_q_heads);
     }
-}
-
-// Fewer workgroups of the 128-row kernel than CUs, at most two 32-row blocks with rows per CU, and no key
-// range split (that takes contexts of 2048 tokens and more, where the 128-row kernel's slices fill the
-// chip): above any of these lines the larger block reads K and V less often and wins.  us for two layers,
-// 128-row kernel against this one -- 512 rows over 512 keys, 32 heads (512 blocks): 83, 72; 4 x 512 over
-// 1500, 8 heads (512): 150, 115; 6 x 256 over 300 to 800, 32 heads (1536): 102, 209; 1536 over 384
-// (1536): 147, 264.
-bool attention_rows_fits(const AttnWork* work, int n_work, int n_groups, int n_q_heads, int n_kv_heads) {
-    if (n_groups != 0 || (int64_t)n_work * (n_q_heads / attention_mfma_heads_per_block(n_q_heads, n_kv_heads)) >= 256)
-        return false;
-    int64_t blocks = 0;
-    for (int i = 0; i < n_work; ++i) blocks += (work[i].n_rows + 31) / 32 * n_q_heads;
-    return blocks <= 512;
-}
-
-void launch_attention_rows(hipStream_t s, const void* q, void* out, const void* pool_layer, const AttnWork* work,
-                           int n_work, const int32_t* page_tables, int n_q_heads, KvGeom g) {
-    if (n_work <= 0) return;
-    // 32-row blocks once whole items of them would give every CU two workgroups, 16-row blocks below
-    const bool two = (int64_t)n_work * (ATTN_BLOCK_ROWS / 32) * n_q_heads >= 512;
-    const dim3 grid((unsigned)n_work * (ATTN_BLOCK_ROWS / (two ? 32 : 16)), n_q_heads);
-#define CF_ROWS(HD, NQ) attention_rows_kernel<HD, NQ><<<grid, 256, 0, s>>>((const bf16*)q, (bf16*)out, (const bf16*)pool_layer, work, page_tables, n_q_heads, g)
-    if (g.head_dim == 128) { if (two) CF_ROWS(128, 2); else CF_ROWS(128, 1); }
-    else { if (two) CF_ROWS(64, 2); else CF_ROWS(64, 1); }
-#undef CF_ROWS
 }
 
 }  // namespace cf

@@ -738,12 +738,7 @@ int run_phase(cf_ctx* c, cf_cache* cache, const Phase& ph, int n_layers_max,
                         }
                         c->prof_begin(CF_K_ATTENTION, pairs * 4.0 * m.n_q_heads * m.head_dim, c->cs);
                     }
-                    // (new-turn rows only: a recomputed row keeps its bits whatever else is in the launch)
-                    if (mfma_attn && part == 1 &&
-                        attention_rows_fits(ph.work.data() + ci.work_off + w0, w1 - w0, g1 - g0, m.n_q_heads, m.n_kv_heads))
-                        launch_attention_rows(c->cs, c->q(), c->o(), pool_layer, d_work + ci.work_off + w0, w1 - w0,
-                                              d_pt, m.n_q_heads, g);
-                    else if (mfma_attn)
+                    if (mfma_attn)
                         launch_attention_mfma(c->cs, c->q(), c->o(), c->attn_part(), pool_layer,
                                               d_work + ci.work_off + w0, w1 - w0, d_grp + ci.grp_off + g0,
                                               g1 - g0, d_pt, m.n_q_heads, g);
