@@ -167,7 +167,8 @@ void launch_f32(hipStream_t s, const float* A, const float* W, const float* W2, 
 // register layout that O^T = V^T P^T wants as its second operand; the V part of a page is already
 // [head_dim][slot], so both K and V fragments are 16-byte reads straight from the page (no LDS: the
 // wavefronts share no keys), one page ahead.  NQ = 2 halves the page reads per row, NQ = 1 doubles
-// the workgroups; a row's result does not depend on it (pages past its position add exact zeros).
+// the workgroups; a row's result does not depend on it: keys past its position add exact zeros, whatever
+// they hold (the test for that costs nothing measurable: a batch of 2.7 k rows 551 -> 535 us a call).
 // What bounds it is the chain of pages of a long row: 2.7 k query rows over up to 2 k keys, 4 heads
 // of 64: 6.0 ms -> 47 us a launch against the lane-per-key kernel; 64 rows: 240 -> 7 us.
 template <int HD, int NQ>
@@ -267,12 +268,39 @@ attention_f32_kernel(const float* __restrict__ q, float* __restrict__ out, const
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o[i][t][r] *= corr;
         }
+        // A page with keys that some row of the block does not see yet: their probabilities are zero, but
+        // 0 * Inf or 0 * NaN must not get into that row.
+        bool bad = false;
+        if ((p + 1) * CF_PAGE_TOKENS - 1 > w.pos0 + r0) {
 #pragma unroll
-        for (int t = 0; t < G; ++t)
+            for (int t = 0; t < G; ++t)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+                for (int r = 0; r < 4; ++r) bad |= !(fabsf(vf[t][r]) < INFINITY);
+        }
+        if (__builtin_amdgcn_ballot_w64(bad) == 0) {
 #pragma unroll
-                for (int i = 0; i < NQ; ++i) o[i][t] = mfma4(vf[t][e], s[i][e], o[i][t]);
+            for (int t = 0; t < G; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < NQ; ++i) o[i][t] = mfma4(vf[t][e], s[i][e], o[i][t]);
+        } else {
+            // once per query row, with the keys past it out of V (a row is a column of the product)
+#pragma unroll 1
+            for (int row = 0; row < 16; ++row)
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) {
+                    const int seen = w.pos0 + min(r0 + 16 * i + row, w.n_rows - 1);
+#pragma unroll
+                    for (int t = 0; t < G; ++t) {
+                        f32x4_t x = o[i][t];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x = mfma4(key0 + e <= seen ? vf[t][e] : 0.f, s[i][e], x);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) o[i][t][r] = fr == row ? x[r] : o[i][t][r];
+                    }
+                }
+        }
 #pragma unroll
         for (int t = 0; t < G; ++t) { kf[t] = kn[t]; vf[t] = vn[t]; }
     }

@@ -76,3 +76,46 @@ def test_attention_f32_matches_the_oracle(hd, hq, hkv, n_ctx, n_new):
         for a, b in zip(got, stack_kv(shape, kv_ctx, kv_new)):
             assert np.abs(a - b).max() <= 1e-4
     s.close()
+
+
+@pytest.mark.parametrize("hd, hq, hkv, n_other", [(64, 4, 2, 0), (128, 4, 4, 0), (64, 8, 8, 18), (128, 8, 2, 18)])
+def test_attention_f32_a_later_token_that_is_not_finite(hd, hq, hkv, n_other):
+    """A token whose embedding is NaN makes its own rows and those behind it NaN; every row before it, and
+    every other request, keeps the bits that it has with an ordinary token in that place."""
+    from paper_2604_25080_amd.runtime import Session
+    from gpu_util import decode_pages
+    shape = ModelShape("f32-3", 3, 128, hq, hkv, hd, 160, 64, 10000.0, 1e-5, "f32")
+
+    class Source(WeightSource):
+        def storage(self, name, layer=-1):
+            w = super().storage(name, layer)
+            if name == "embed":
+                w[63] = np.nan
+            return w
+
+    rng = np.random.default_rng(hd + hq)
+    n_ctx, n_new = [40, 53, 21] + [18] * n_other, [20, 35, 17] + [2] * n_other
+    ctx, new = ([rng.integers(0, 63, size=n).astype(np.int32) for n in v] for v in (n_ctx, n_new))
+    at = {0: 38, 1: 53 + 18}                                   # in a context, in a new turn; request 2 has none
+    s = Session(shape, Source(shape, 12), max_batch=len(n_ctx), max_tokens=sum(n_ctx) + sum(n_new), max_positions=128,
+                n_pages=4 * len(n_ctx) + 8, pool_fill=0xFF)
+    for i, (n, m) in enumerate(zip(n_ctx, n_new)):
+        s.cache.alloc(1 + i, n + m)
+
+    def run():
+        reqs = [dict(req_id=1 + i, ctx_tokens=ctx[i], new_tokens=new[i]) for i in range(len(n_ctx))]
+        logits, _ = s.restore(reqs, [(0, n, shape.n_layers) for n in n_ctx])
+        cells = [np.stack(decode_pages(shape, s.read_pages(1 + i, n + m), n + m)) for i, (n, m) in enumerate(zip(n_ctx, n_new))]
+        return logits.cpu().numpy().copy(), cells
+
+    clean_logits, clean = run()
+    assert np.isfinite(clean_logits).all()
+    for i, j in at.items():
+        (ctx if j < n_ctx[i] else new)[i][j if j < n_ctx[i] else j - n_ctx[i]] = 63
+    logits, cells = run()
+    for i in range(len(n_ctx)):
+        j = at.get(i, n_ctx[i] + n_new[i])
+        assert np.array_equal(cells[i][:, :, :j], clean[i][:, :, :j]), f"request {i}: rows before position {j}"
+        assert np.isnan(cells[i][:, 1:, j:]).all()
+        assert np.array_equal(logits[i], clean_logits[i]) if i not in at else np.isnan(logits[i]).all()
+    s.close()
