@@ -678,8 +678,7 @@ int run_phase(cf_ctx* c, cf_cache* cache, const Phase& ph, int n_layers_max,
                 launch_rmsnorm(c->cs, m.dtype, h_rows + (size_t)x * d, l > 0 ? dl_rows + (size_t)x * d : nullptr,
                                lw.attn_norm, a_buf, Tc, d, m.rms_eps, nullptr);
                 c->prof_end(CF_K_RMSNORM, c->cs);
-                if (!c->simple_only && gemm_mfma_qkv_rope_supported(m.dtype, Tc, qcols, d, m.head_dim) &&
-                    gemm_mfma_aligned(a_buf, lw.wqkv, nullptr)) {
+                if (!c->simple_only && gemm_mfma_qkv_rope_supported(m.dtype, Tc, qcols, d, m.head_dim)) {
                     // RoPE and the page write happen on the accumulators of the QKV projection
                     const RopeEpilogue re{d_pos + x, d_slot + x, c->rope(), pool_layer, m.n_q_heads, g};
                     c->prof_begin(CF_K_GEMM_QKV, 2.0 * Tc * (double)qcols * d, c->cs);

@@ -31,6 +31,7 @@ namespace cf {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;   // native 16-byte register vector
+typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;            // the same in memory, at any element
 
 namespace {
 
@@ -135,10 +136,12 @@ __device__ __forceinline__ void store_tile(const f32x4_t (&acc)[FM][FN], float* 
     }
 }
 
-// BM x BN block tile by NWM x NWN wavefronts; SA (SB) K-steps of A (B) in LDS.
+// BM x BN block tile by NWM x NWN wavefronts; SA (SB) K-steps of A (B) in LDS.  DIRECT: operands go
+// straight to LDS, which takes starts on whole dwords and tiles within 32-bit offsets; otherwise they
+// go through registers (see Tile).
 // `bid` of `nb` workgroups walk the tiles_m x tiles_n tiles whose origin is (m_off, n_off); M, N
 // are the bounds of the whole matrix.
-template <int EPI, int BM, int BN, int NWM, int NWN, int SA, int SB>
+template <int EPI, int BM, int BN, int NWM, int NWN, int SA, int SB, bool DIRECT>
 __device__ __forceinline__ void
 gemm_mfma_body(char* smem, const bf16* __restrict__ A, const bf16* __restrict__ W,
                const bf16* __restrict__ W2, float* __restrict__ Cf, bf16* __restrict__ Dt, int M,
@@ -258,68 +261,215 @@ gemm_mfma_body(char* smem, const bf16* __restrict__ A, const bf16* __restrict__ 
         for (int i = 0; i < FM; ++i) fa[i] = read_a(sa, kk, i);
     };
 
-    // ---- main loop over K-steps of 64.  Step t sits in stage t % SA of A and t % SB of B.  Half-way
-    // through step t every wavefront has read all of it (the second half's fragments are in
-    // registers): one barrier says so, and that step t + 1 has landed; the stages are then refilled
-    // with steps t + SA and t + SB.  Of an operand with a stage more the loads go last and stay in
-    // flight over a second barrier.
-    constexpr int LOADS = LA + LB, LEFT = (S - 2) * LOADS + XA * LA + XB * LB;
+    if constexpr (!DIRECT) {
+        // ---- through registers, two K-steps in LDS; the K order of an element, and so its bits, are those of
+        // the loop below.  Past the row's end its last chunk is read again: its place in LDS is zeroed (in the
+        // last step) or never multiplied (in a step past the end).
+        static_assert(SA == 2 && SB == 2, "two K-steps in LDS");
+        const int64_t row_bytes = (int64_t)K * 2;
+        const char* a_tile = (const char*)(A + (int64_t)m0 * K);
+        auto b_tile = [&](int j) { return (const char*)(SILU && j >= LB1 ? w2_tile : w_tile); };
+        const char* pa[LA];
+        const char* pb[LB];
+        if constexpr (!BIG) {
 #pragma unroll
-    for (int t = 0; t < SA || t < SB; ++t)
-        if (t < nk) {
+            for (int j = 0; j < LA; ++j) pa[j] = a_tile + min(ld_row + j * NW * 8, rows_a - 1) * row_bytes;
 #pragma unroll
-            for (int j = 0; j < LA && t < SA; ++j) dma_a(t, t, j);
-#pragma unroll
-            for (int j = 0; j < LB && t < SB; ++j) dma_b(t, t, j);
+            for (int j = 0; j < LB; ++j) pb[j] = b_tile(j) + min(ld_row + j % LB1 * NW * 8, rows_b - 1) * row_bytes;
         }
-    if (nk >= S + XA + XB) wait_barrier<LEFT + LOADS>();
-    else wait_barrier<0>();
-    read_frags(fa0, fb0, 0, 0, 0);
-    int ca = 0, cb = 0;                           // the current step's stages
-    // refill 2: both operands; 1: only the one without the extra stage; 0: none
-    auto kstep = [&](int kt, auto refill) {
-        constexpr int REFILL = refill.value;
-        const int na = ca + 1 == SA ? 0 : ca + 1, nb_ = cb + 1 == SB ? 0 : cb + 1;
-        read_frags(fa1, fb1, ca, cb, 1);
+        auto get = [&](const char* tile, const char* row, int kt, int j) {
+            if constexpr (BIG)                    // one base per tile, 32-bit offsets (host: K < 2^23)
+                return *reinterpret_cast<const u32x4_any_t*>(tile + (va[0] + (j * (NW * 8) * row_b + (unsigned)min(kt, nk - 1) * ROW_BYTES)));
+            else
+                return *reinterpret_cast<const u32x4_any_t*>(row + min((int64_t)kt * ROW_BYTES + ld_col, row_bytes - 16));
+        };
+        auto get_a = [&](int kt, int j) { return get(a_tile, pa[j], kt, j); };
+        auto get_b = [&](int kt, int j) { return get(b_tile(j), pb[j], kt, j % LB1); };
+        char* const st = smem + (wave * 64 + lane) * 16;
+        auto put = [&](char* at, u32x4_t v, int kt) {
+            if (!BIG && kt == last && past) v = u32x4_t{0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4_t*>(at) = v;
+        };
+        auto put_a = [&](int kt, int j, u32x4_t v) { put(st + (kt & 1) * A_TILE + j * (NW * 1024), v, kt); };
+        auto put_b = [&](int kt, int j, u32x4_t v) { put(st + A_ALL + (kt & 1) * B_TILE + j * (NW * 1024), v, kt); };
+        if constexpr (BIG) {
+            // Registers for four loads are left beside two wavefronts per SIMD: A and B take turns, half a step
+            // between a load and its way to LDS.  B runs a step ahead of A, into the stage that the barrier
+            // has just freed.
+            static_assert(LA == LB && LA <= FM, "one load beside each row of MFMAs");
+            u32x4_t r[LA];
+            auto fill_b = [&](int kt) {
 #pragma unroll
-        for (int i = 0; i < FM; ++i) mfma_row(fa0, fb0, i);
-        constexpr int RPM = (FM * FN) / (FM + FN);            // MFMAs per fragment read
+                for (int j = 0; j < LB; ++j) put_b(kt, j, get_b(kt, j));
+            };
 #pragma unroll
-        for (int u = 0; u < FM + FN; ++u) {
-            __builtin_amdgcn_sched_group_barrier(0x8, RPM, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x8, FM * FN - RPM * (FM + FN), 0);
-        if constexpr (REFILL == 2) wait_barrier<LEFT>();
-        else wait_barrier<0>();
+            for (int j = 0; j < LA; ++j) put_a(0, j, get_a(0, j));
+            fill_b(0);
+            fill_b(1);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            // the next fragments and the refill, spread over the rows of MFMAs; the priority keeps
-            // the other wavefront of the SIMD from breaking into the row (gate/up: +3 %)
-            constexpr int PJ = (FN + FM - 1) / FM;
-            constexpr int FIRST = XB ? LA : LB, N_REFILL = REFILL == 2 ? LOADS : REFILL == 1 ? FIRST : 0;
-            constexpr int PD = (LOADS + FM - 1) / FM;
+            for (int j = 0; j < LA; ++j) r[j] = get_a(1, j);
+            __syncthreads();
+            read_frags(fa0, fb0, 0, 0, 0);
+            constexpr int PJ = FN / FM;
+            auto step = [&](int kt, auto parity) {    // parity of kt: the LDS offsets are constants
+                constexpr int cur = parity.value;
 #pragma unroll
-            for (int j = i * PJ; j < (i + 1) * PJ && j < FN; ++j) fb0[j] = read_b(nb_, 0, j);
-            fa0[i] = read_a(na, 0, i);
+                for (int i = 0; i < FM; ++i) {
 #pragma unroll
-            for (int j = i * PD; j < (i + 1) * PD && j < N_REFILL; ++j) {
-                if ((j < FIRST) == (XB > 0)) dma_a(kt + SA, ca, j < FIRST ? j : j - FIRST);
-                else dma_b(kt + SB, cb, j < FIRST ? j : j - FIRST);
+                    for (int j = i * PJ; j < (i + 1) * PJ; ++j) fb1[j] = read_b(cur, 1, j);
+                    fa1[i] = read_a(cur, 1, i);
+                    if (i < LA) {
+                        put_a(cur ^ 1, i, r[i]);
+                        r[i] = get_b(kt + 2, i);
+                    }
+                    mfma_row(fa0, fb0, i);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+#pragma unroll
+                    for (int j = i * PJ; j < (i + 1) * PJ; ++j) fb0[j] = read_b(cur ^ 1, 0, j);
+                    fa0[i] = read_a(cur ^ 1, 0, i);
+                    if (i < LA) {
+                        put_b(cur, i, r[i]);
+                        r[i] = get_a(kt + 2, i);
+                    }
+                    mfma_row(fa1, fb1, i);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            for (int kt = 0; kt < nk; kt += 2) {      // K is whole pairs of steps (host)
+                step(kt, std::integral_constant<int, 0>{});
+                step(kt + 1, std::integral_constant<int, 1>{});
             }
-            __builtin_amdgcn_s_setprio(1);
-            mfma_row(fa1, fb1, i);
-            __builtin_amdgcn_s_setprio(0);
-            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            constexpr int D = BM == 128 ? 2 : 4;  // K-steps in flight in registers
+            u32x4_t ra[D][LA], rb[D][LB];
+#pragma unroll
+            for (int t = 0; t <= D; ++t) {
+                if (t == D) {
+#pragma unroll
+                    for (int j = 0; j < LA; ++j) put_a(0, j, ra[0][j]);
+#pragma unroll
+                    for (int j = 0; j < LB; ++j) put_b(0, j, rb[0][j]);
+                }
+#pragma unroll
+                for (int j = 0; j < LA; ++j) ra[t % D][j] = get_a(t, j);
+#pragma unroll
+                for (int j = 0; j < LB; ++j) rb[t % D][j] = get_b(t, j);
+            }
+            __syncthreads();
+            read_frags(fa0, fb0, 0, 0, 0);
+            auto step = [&](int kt, auto set) {   // set: the registers that hold step kt + 1
+                constexpr int X = set.value, PJ = (FN + FM - 1) / FM, PA = (LA + FM - 1) / FM, PB = (LB + FM - 1) / FM;
+                const int cur = kt & 1;
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+                    // beside a row of MFMAs: the second half's fragments, and step kt + 1 goes to LDS and makes
+                    // room for step kt + 1 + D
+#pragma unroll
+                    for (int j = i * PJ; j < (i + 1) * PJ && j < FN; ++j) fb1[j] = read_b(cur, 1, j);
+                    fa1[i] = read_a(cur, 1, i);
+#pragma unroll
+                    for (int j = i * PA; j < (i + 1) * PA && j < LA; ++j) {
+                        put_a(kt + 1, j, ra[X][j]);
+                        ra[X][j] = get_a(kt + 1 + D, j);
+                    }
+#pragma unroll
+                    for (int j = i * PB; j < (i + 1) * PB && j < LB; ++j) {
+                        put_b(kt + 1, j, rb[X][j]);
+                        rb[X][j] = get_b(kt + 1 + D, j);
+                    }
+                    mfma_row(fa0, fb0, i);
+                }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < FM; ++i) {
+#pragma unroll
+                    for (int j = i * PJ; j < (i + 1) * PJ && j < FN; ++j) fb0[j] = read_b(cur ^ 1, 0, j);
+                    fa0[i] = read_a(cur ^ 1, 0, i);
+                    mfma_row(fa1, fb1, i);
+                }
+            };
+            // whole groups without a branch: across one the compiler moves the loads down to their use
+            int kt = 0;
+            for (; kt + D <= nk; kt += D) {
+                step(kt, std::integral_constant<int, 1 % D>{});
+                step(kt + 1, std::integral_constant<int, 2 % D>{});
+                if constexpr (D > 2) {
+                    step(kt + 2, std::integral_constant<int, 3 % D>{});
+                    step(kt + 3, std::integral_constant<int, 0>{});
+                }
+            }
+            if (kt < nk) step(kt++, std::integral_constant<int, 1 % D>{});
+            if (D > 2 && kt < nk) step(kt++, std::integral_constant<int, 2 % D>{});
+            if (D > 2 && kt < nk) step(kt++, std::integral_constant<int, 3 % D>{});
         }
-        ca = na;
-        cb = nb_;
-    };
-    int kt = 0;
-    for (; kt + S + XA + XB < nk; ++kt) kstep(kt, std::integral_constant<int, 2>{});
-    if constexpr (XA + XB > 0)
-        if (kt + S < nk) kstep(kt++, std::integral_constant<int, 1>{});
-    for (; kt < nk; ++kt) kstep(kt, std::integral_constant<int, 0>{});
+    } else {
+        // ---- main loop over K-steps of 64.  Step t sits in stage t % SA of A and t % SB of B.  Half-way
+        // through step t every wavefront has read all of it (the second half's fragments are in
+        // registers): one barrier says so, and that step t + 1 has landed; the stages are then refilled
+        // with steps t + SA and t + SB.  Of an operand with a stage more the loads go last and stay in
+        // flight over a second barrier.
+        constexpr int LOADS = LA + LB, LEFT = (S - 2) * LOADS + XA * LA + XB * LB;
+#pragma unroll
+        for (int t = 0; t < SA || t < SB; ++t)
+            if (t < nk) {
+#pragma unroll
+                for (int j = 0; j < LA && t < SA; ++j) dma_a(t, t, j);
+#pragma unroll
+                for (int j = 0; j < LB && t < SB; ++j) dma_b(t, t, j);
+            }
+        if (nk >= S + XA + XB) wait_barrier<LEFT + LOADS>();
+        else wait_barrier<0>();
+        read_frags(fa0, fb0, 0, 0, 0);
+        int ca = 0, cb = 0;                           // the current step's stages
+        // refill 2: both operands; 1: only the one without the extra stage; 0: none
+        auto kstep = [&](int kt, auto refill) {
+            constexpr int REFILL = refill.value;
+            const int na = ca + 1 == SA ? 0 : ca + 1, nb_ = cb + 1 == SB ? 0 : cb + 1;
+            read_frags(fa1, fb1, ca, cb, 1);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) mfma_row(fa0, fb0, i);
+            constexpr int RPM = (FM * FN) / (FM + FN);            // MFMAs per fragment read
+#pragma unroll
+            for (int u = 0; u < FM + FN; ++u) {
+                __builtin_amdgcn_sched_group_barrier(0x8, RPM, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x8, FM * FN - RPM * (FM + FN), 0);
+            if constexpr (REFILL == 2) wait_barrier<LEFT>();
+            else wait_barrier<0>();
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+                // the next fragments and the refill, spread over the rows of MFMAs; the priority keeps
+                // the other wavefront of the SIMD from breaking into the row (gate/up: +3 %)
+                constexpr int PJ = (FN + FM - 1) / FM;
+                constexpr int FIRST = XB ? LA : LB, N_REFILL = REFILL == 2 ? LOADS : REFILL == 1 ? FIRST : 0;
+                constexpr int PD = (LOADS + FM - 1) / FM;
+#pragma unroll
+                for (int j = i * PJ; j < (i + 1) * PJ && j < FN; ++j) fb0[j] = read_b(nb_, 0, j);
+                fa0[i] = read_a(na, 0, i);
+#pragma unroll
+                for (int j = i * PD; j < (i + 1) * PD && j < N_REFILL; ++j) {
+                    if ((j < FIRST) == (XB > 0)) dma_a(kt + SA, ca, j < FIRST ? j : j - FIRST);
+                    else dma_b(kt + SB, cb, j < FIRST ? j : j - FIRST);
+                }
+                __builtin_amdgcn_s_setprio(1);
+                mfma_row(fa1, fb1, i);
+                __builtin_amdgcn_s_setprio(0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            ca = na;
+            cb = nb_;
+        };
+        int kt = 0;
+        for (; kt + S + XA + XB < nk; ++kt) kstep(kt, std::integral_constant<int, 2>{});
+        if constexpr (XA + XB > 0)
+            if (kt + S < nk) kstep(kt++, std::integral_constant<int, 1>{});
+        for (; kt < nk; ++kt) kstep(kt, std::integral_constant<int, 0>{});
+    }
 
     // ---- epilogue.  Fragment (i, j): output row 16 i + lane % 16, columns 16 j + 4 (lane / 16) + r:
     // a lane stores its four columns as one vector.  The big tile lies wholly inside the matrix
@@ -415,18 +565,23 @@ gemm_mfma_body(char* smem, const bf16* __restrict__ A, const bf16* __restrict__ 
 // The block tiles: wavefront grid and K-steps of A and B in LDS.  Of the 160 KB two steps of the
 // big tile take 128; the third step of B lets its loads take two steps to land (down projection,
 // K = 14336, 8192 rows: 1.33 -> 1.41 PFLOP/s; K = 4096: no change).
-template <int TILE> struct Tile;
-template <> struct Tile<256> { static constexpr int NWM = 4, NWN = 2, SA = 2, SB = 3; };
-template <> struct Tile<128> { static constexpr int NWM = 2, NWN = 2, SA = 2, SB = 2; };
-template <> struct Tile<64> { static constexpr int NWM = 2, NWN = 2, SA = 4, SB = 4; };
+// Operands that cannot go straight to LDS (an odd element, rows of 2^22 elements and more) go through
+// registers: unaligned 16-byte loads and the way back cost a fifth to a half (13 389 rows x 4096 x 14336: 1711 us
+// against 1220; 1000 x 4096 x 4096: 57, 45; 33 x 6144 x 4096: 22, 15), the plain kernel 15 to 60 times that.
+template <int TILE, bool DIRECT> struct Tile;
+template <> struct Tile<256, true> { static constexpr int NWM = 4, NWN = 2, SA = 2, SB = 3; };
+template <> struct Tile<128, true> { static constexpr int NWM = 2, NWN = 2, SA = 2, SB = 2; };
+template <> struct Tile<64, true> { static constexpr int NWM = 2, NWN = 2, SA = 4, SB = 4; };
+template <int TILE> struct Tile<TILE, false> { static constexpr int NWM = TILE == 256 ? 4 : 2, NWN = 2, SA = 2, SB = 2; };
 
-template <int EPI, int B>
-__global__ void __launch_bounds__(64 * Tile<B>::NWM * Tile<B>::NWN, 2)
+template <int EPI, int B, bool DIRECT>
+__global__ void __launch_bounds__((64 * Tile<B, DIRECT>::NWM * Tile<B, DIRECT>::NWN), 2)
 gemm_mfma_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
                  const bf16* __restrict__ W2, float* __restrict__ Cf, bf16* __restrict__ Dt, int M,
                  int N, int K, int tiles_m, int tiles_n, RopeEpilogue rope) {
     extern __shared__ __align__(16) char smem[];
-    gemm_mfma_body<EPI, B, B, Tile<B>::NWM, Tile<B>::NWN, Tile<B>::SA, Tile<B>::SB>(
+    using T = Tile<B, DIRECT>;
+    gemm_mfma_body<EPI, B, B, T::NWM, T::NWN, T::SA, T::SB, DIRECT>(
         smem, A, W, W2, Cf, Dt, M, N, K, tiles_m, tiles_n, 0, 0, (int)blockIdx.x, tiles_m * tiles_n, rope);
 }
 
@@ -449,10 +604,10 @@ gemm_mfma_tail_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
     extern __shared__ __align__(16) char smem[];
     const RopeEpilogue none{};
     if ((int)blockIdx.x < n_big)
-        gemm_mfma_body<EPI, 256, 256, 4, 2, Tile<256>::SA, Tile<256>::SB>(smem, A, W, W2, Cf, Dt, M, N, K, tiles_m, tiles_n, 0, 0,
-                                               (int)blockIdx.x, n_big, none);
+        gemm_mfma_body<EPI, 256, 256, 4, 2, Tile<256, true>::SA, Tile<256, true>::SB, true>(
+            smem, A, W, W2, Cf, Dt, M, N, K, tiles_m, tiles_n, 0, 0, (int)blockIdx.x, n_big, none);
     else
-        gemm_mfma_body<EPI, 128, 128, 4, 2, 4, 4>(smem, A, W, W2, Cf, Dt, M, N, K, tail_tiles_m, tail_tiles_n,
+        gemm_mfma_body<EPI, 128, 128, 4, 2, 4, 4, true>(smem, A, W, W2, Cf, Dt, M, N, K, tail_tiles_m, tail_tiles_n,
                                                tail_m_off, tail_n_off, (int)blockIdx.x - n_big,
                                                tail_tiles_m * tail_tiles_n, none);
 }
@@ -546,13 +701,13 @@ gemm_rows_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W, float* 
 constexpr int N_CUS = 256;            // MI355X
 constexpr int GROUP_M = 8;            // tile rows per group of the tile order (see the body)
 
-template <int EPI, int B>
+template <int EPI, int B, bool DIRECT>
 void launch_tile(hipStream_t s, const void* A, const void* W, const void* W2, float* Cf, void* Dt,
                  int M, int N, int K, bool tail_ok = false, const RopeEpilogue& rope = RopeEpilogue{}) {
     constexpr int BN_OUT = (EPI == EPI_SILU_MUL) ? B / 2 : B;
-    constexpr int LDS = (Tile<B>::SA + Tile<B>::SB) * B * ROW_BYTES;
+    constexpr int LDS = (Tile<B, DIRECT>::SA + Tile<B, DIRECT>::SB) * B * ROW_BYTES;
     int tiles_m = (M + B - 1) / B, tiles_n = (N + BN_OUT - 1) / BN_OUT;
-    if constexpr (B == 256 && EPI != EPI_ADD_F32 && EPI != EPI_QKV_ROPE128 && EPI != EPI_QKV_ROPE64) {
+    if constexpr (B == 256 && DIRECT && EPI != EPI_ADD_F32 && EPI != EPI_QKV_ROPE128 && EPI != EPI_QKV_ROPE64) {
         // tail: the last nb % N_CUS tiles, rounded up to whole columns of the last row group
         const int nb = tiles_m * tiles_n, tail = nb % N_CUS;
         const int gsz = tiles_m - (tiles_m - 1) / GROUP_M * GROUP_M;       // rows of the last group
@@ -574,12 +729,12 @@ void launch_tile(hipStream_t s, const void* A, const void* W, const void* W2, fl
         }
     }
     static bool configured = false;
-    auto kern = gemm_mfma_kernel<EPI, B>;
+    auto kern = gemm_mfma_kernel<EPI, B, DIRECT>;
     if (!configured) {
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         configured = true;
     }
-    kern<<<tiles_m * tiles_n, 64 * Tile<B>::NWM * Tile<B>::NWN, LDS, s>>>((const bf16*)A, (const bf16*)W, (const bf16*)W2, Cf,
+    kern<<<tiles_m * tiles_n, 64 * Tile<B, DIRECT>::NWM * Tile<B, DIRECT>::NWN, LDS, s>>>((const bf16*)A, (const bf16*)W, (const bf16*)W2, Cf,
                                              (bf16*)Dt, M, N, K, tiles_m, tiles_n, rope);
 }
 
@@ -605,18 +760,18 @@ inline bool prefer_big(int M, int N, int bn_out128) {
     return (int64_t)((M + 127) / 128) * ((N + bn_out128 - 1) / bn_out128) > 2 * N_CUS;
 }
 
-template <int EPI>
+template <int EPI, bool DIRECT>
 void launch(hipStream_t s, const void* A, const void* W, const void* W2, float* Cf, void* Dt, int M,
             int N, int K) {
     constexpr int BN_OUT128 = EPI == EPI_SILU_MUL ? 64 : 128;
-    const bool big = (g_force_tile ? g_force_tile >= 256 : prefer_big(M, N, BN_OUT128)) && K % (2 * BK) == 0 &&
+    const bool big = (g_force_tile ? g_force_tile >= 256 : prefer_big(M, N, BN_OUT128)) && K % (2 * BK) == 0 && K < (1 << 23) &&
                      M >= 256 && N >= 2 * BN_OUT128 && EPI != EPI_ADD_F32;
-    if (big) { launch_tile<EPI, 256>(s, A, W, W2, Cf, Dt, M, N, K, g_force_tile == 0 || g_force_tile == 257); return; }
+    if (big) { launch_tile<EPI, 256, DIRECT>(s, A, W, W2, Cf, Dt, M, N, K, g_force_tile == 0 || g_force_tile == 257); return; }
     // At most 32 rows: the few-row kernel, unless the weight is so wide (an LM head) that larger
     // column tiles fill the chip anyway (us, 64x64 tiles against it -- N 4096, K 14336, 16 rows: 42,
     // 23; N 1280, K 8192: 25, 14; N 6144, K 4096, 23 rows: 14, 10; N 128256: 188 with 128x128
     // tiles against 205).  The gate/up pair has twice the columns and does better on the 64 tile.
-    if constexpr (EPI != EPI_SILU_MUL)
+    if constexpr (EPI != EPI_SILU_MUL && DIRECT)
         if (g_force_tile == 0 && M <= 32 && N <= 32 * ROWS_MAX_WG) {
             if (M <= 16) launch_rows<EPI, 16, 32, 4, 3>(s, A, W, Cf, Dt, M, N, K);
             else launch_rows<EPI, 32, 32, 4, 3>(s, A, W, Cf, Dt, M, N, K);
@@ -629,8 +784,8 @@ void launch(hipStream_t s, const void* A, const void* W, const void* W2, float* 
     // not depend on the choice.
     const int64_t tiles64 = (int64_t)((M + 63) / 64) * ((N + BN_OUT128 / 2 - 1) / (BN_OUT128 / 2));
     const bool small = g_force_tile ? g_force_tile == 64 : tiles64 <= 3 * N_CUS;
-    if (small) launch_tile<EPI, 64>(s, A, W, W2, Cf, Dt, M, N, K);
-    else launch_tile<EPI, 128>(s, A, W, W2, Cf, Dt, M, N, K);
+    if (small) launch_tile<EPI, 64, DIRECT>(s, A, W, W2, Cf, Dt, M, N, K);
+    else launch_tile<EPI, 128, DIRECT>(s, A, W, W2, Cf, Dt, M, N, K);
 }
 
 }  // namespace
@@ -645,12 +800,18 @@ bool gemm_mfma_qkv_rope_supported(int dtype, int M, int N, int K, int head_dim) 
            N % 256 == 0 && K >= 2 * BK && K % (2 * BK) == 0;
 }
 
+// Straight to LDS: the loads move whole dwords at 32-bit offsets within a tile's rows.
+static bool direct_ok(const void* A, const void* W, const void* W2, int K) {
+    return (((uintptr_t)A | (uintptr_t)W | (uintptr_t)W2) & 3) == 0 && K < (1 << 22);
+}
+
 void launch_gemm_mfma_qkv_rope(hipStream_t s, const void* A, const void* Wqkv, void* q_out, int M,
                                int N, int K, const RopeEpilogue& rope) {
-    if (rope.g.head_dim == 128)
-        launch_tile<EPI_QKV_ROPE128, 256>(s, A, Wqkv, nullptr, nullptr, q_out, M, N, K, false, rope);
-    else
-        launch_tile<EPI_QKV_ROPE64, 256>(s, A, Wqkv, nullptr, nullptr, q_out, M, N, K, false, rope);
+    const bool direct = direct_ok(A, Wqkv, nullptr, K);
+#define CF_QKV(EPI, DIRECT) launch_tile<EPI, 256, DIRECT>(s, A, Wqkv, nullptr, nullptr, q_out, M, N, K, false, rope)
+    if (rope.g.head_dim == 128) { if (direct) CF_QKV(EPI_QKV_ROPE128, true); else CF_QKV(EPI_QKV_ROPE128, false); }
+    else { if (direct) CF_QKV(EPI_QKV_ROPE64, true); else CF_QKV(EPI_QKV_ROPE64, false); }
+#undef CF_QKV
 }
 
 bool gemm_mfma_supported(int dtype, int M, int N, int K, int epi) {
@@ -659,25 +820,20 @@ bool gemm_mfma_supported(int dtype, int M, int N, int K, int epi) {
 }
 
 bool gemm_mfma_takes(int dtype, int M, int N, int K) {
-    return dtype == CF_BF16 && M > 0 && N > 0 && K >= BK && K % 8 == 0 && K < (1 << 22);
-}
-
-bool gemm_mfma_aligned(const void* A, const void* W, const void* W2) {
-    return (((uintptr_t)A | (uintptr_t)W | (uintptr_t)W2) & 3) == 0;
+    return dtype == CF_BF16 && M > 0 && N > 0 && K >= BK && K % 8 == 0;
 }
 
 void launch_gemm_mfma(hipStream_t s, const void* A, const void* W, const void* W2, float* Cf,
                       void* Dt, int M, int N, int K, int epi) {
-    if (!gemm_mfma_aligned(A, W, W2)) {
-        launch_gemm_simple(s, CF_BF16, A, W, W2, Cf, Dt, M, N, K, epi);
-        return;
-    }
+    const bool direct = direct_ok(A, W, W2, K);
+#define CF_GEMM(EPI) if (direct) launch<EPI, true>(s, A, W, W2, Cf, Dt, M, N, K); else launch<EPI, false>(s, A, W, W2, Cf, Dt, M, N, K)
     switch (epi) {
-        case EPI_STORE_F32: launch<EPI_STORE_F32>(s, A, W, W2, Cf, Dt, M, N, K); break;
-        case EPI_ADD_F32: launch<EPI_ADD_F32>(s, A, W, W2, Cf, Dt, M, N, K); break;
-        case EPI_STORE_T: launch<EPI_STORE_T>(s, A, W, W2, Cf, Dt, M, N, K); break;
-        default: launch<EPI_SILU_MUL>(s, A, W, W2, Cf, Dt, M, N, K); break;
+        case EPI_STORE_F32: CF_GEMM(EPI_STORE_F32); break;
+        case EPI_ADD_F32: CF_GEMM(EPI_ADD_F32); break;
+        case EPI_STORE_T: CF_GEMM(EPI_STORE_T); break;
+        default: CF_GEMM(EPI_SILU_MUL); break;
     }
+#undef CF_GEMM
 }
 
 }  // namespace cf

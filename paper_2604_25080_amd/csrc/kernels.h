@@ -79,12 +79,9 @@ void launch_gemm_f32(hipStream_t s, const void* A, const void* W, const void* W2
                      int epi);
 // true if the MFMA kernel supports this problem (bf16, aligned K)
 bool gemm_mfma_supported(int dtype, int M, int N, int K, int epi);
-// what launch_gemm_mfma itself needs: rows of whole 16-byte vectors (the caller of a forced tile is held
-// to whole K-steps of 64 by gemm_mfma_supported)
+// what launch_gemm_mfma itself needs: rows of whole 16-byte vectors, starting at any element (the caller
+// of a forced tile is held to whole K-steps of 64 by gemm_mfma_supported)
 bool gemm_mfma_takes(int dtype, int M, int N, int K);
-// true if the operands start on whole dwords (the loads to LDS move dwords): launch_gemm_mfma hands
-// others -- a matrix that starts at an odd element of a larger buffer -- to the plain kernel
-bool gemm_mfma_aligned(const void* A, const void* W, const void* W2);
 void gemm_mfma_force_tile(int tile);   // 0 = heuristic, 256 or 128 = forced (tuning)
 void launch_gemm_mfma(hipStream_t s, const void* A, const void* W, const void* W2, float* Cf,
                       void* Dt, int M, int N, int K, int epi);

@@ -273,6 +273,40 @@ def test_small_shape_end_to_end_on_the_big_gemm_tile(shape_name):
         sess.close()
 
 
+@pytest.mark.parametrize("shape_name", ["mini-bf16", "mini64-gqa2-bf16"])
+def test_weights_that_start_at_odd_elements_give_the_same_bits(shape_name, monkeypatch):
+    """Matrices one element into their allocations, through the tiles of the heuristic and through the 256x256
+    tile with its fused QKV epilogue: caches and logits as with matrices on 16-byte boundaries."""
+    import paper_2604_25080_amd as cf
+    from paper_2604_25080_amd import runtime
+
+    def odd(arr, device, plain=runtime._to_device):
+        t = plain(arr, device)
+        held = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        held[1:] = t.view(-1)
+        return held[1:].view(t.shape)
+
+    outs = []
+    for at_odd in (False, True):
+        if at_odd:
+            monkeypatch.setattr(runtime, "_to_device", odd)
+        b, refs, sess, host = build(shape_name, 16, 3, 300, 700, 40, 150, chunk_rows=2048)
+        assert (sess.weights[("wqkv", 0)].data_ptr() % 4 == 2) == at_odd
+        try:
+            splits = [(n // 2 // 16 * 16, b.shape.n_layers) for n in b.n_ctx]
+            for force in (0, 256):
+                cf.lib.cf_debug_force_gemm_tile(force)
+                try:
+                    outs.append(restore_and_compare(b, refs, sess, host, splits, seed=73)[0])
+                finally:
+                    cf.lib.cf_debug_force_gemm_tile(0)
+        finally:
+            sess.close()
+    for out in outs[1:]:
+        for i in out:
+            assert all(np.array_equal(x, y) for x, y in zip(out[i], outs[0][i]))
+
+
 def _token_bits(shape, raw, n_tokens):
     """raw uint8 [L, P, page_bytes] of a bf16 cache -> (K, V) uint16 [L, n_tokens, Hkv, hd]: the
     stored bits, token-major (K part [head][slot][hd], V part [head][hd][slot] in a page)."""

@@ -152,7 +152,7 @@ def test_gemm_few_rows_and_ragged_k(sess, rows, nk):
 
 @pytest.mark.parametrize("at_a, at_w", [(2, 0), (0, 6), (1, 0), (0, 3)])
 def test_gemm_operands_that_start_inside_a_larger_buffer(sess, at_a, at_w):
-    """Whole-dword starts take the matrix-core kernel, odd elements the plain one; 2^-24 per term."""
+    """Whole-dword starts are loaded straight to LDS, odd elements through registers; 2^-24 per term."""
     import paper_2604_25080_amd as cf
     M, N, K = 130, 200, 192
     g = torch.Generator().manual_seed(at_a + 10 * at_w)
@@ -161,6 +161,52 @@ def test_gemm_operands_that_start_inside_a_larger_buffer(sess, at_a, at_w):
     sess.ctx.op_gemm(A.data_ptr() + 2 * at_a, W.data_ptr() + 2 * at_w, 0, Cf.data_ptr(), 0, M, N, K, cf.EPI_STORE_F32, 0)
     x, y = a[at_a:at_a + M * K].view(M, K).double(), w[at_w:at_w + N * K].view(N, K).double()
     assert bool(((Cf.cpu().double() - x @ y.t()).abs() <= K * 2.0 ** -24 * (x.abs() @ y.abs().t())).all())
+
+
+@pytest.mark.parametrize("mnk", [(1, 96, 64), (16, 1280, 1024), (33, 130, 72), (300, 544, 512), (700, 2001, 712),
+                                 (1700, 2000, 712), (2900, 3075, 256)])
+def test_gemm_operands_at_odd_elements_give_the_same_bits(sess, mnk):
+    """Every tile (forced where the call takes that: K of whole steps), float and 16-bit outputs, operands
+    followed by NaN; against the same operands on 16-byte boundaries."""
+    import paper_2604_25080_amd as cf
+    M, N, K = mnk
+    g = torch.Generator().manual_seed(M + N + K)
+    parts = [(torch.randn(r * K, generator=g) * std).bfloat16() for r, std in ((M, 1.0), (N, 0.05), (N, 0.05))]
+
+    def placed(x, at):
+        t = torch.full((x.numel() + 64,), float("nan")).bfloat16()
+        t[at:at + x.numel()] = x
+        return t.cuda()[at:]
+
+    even, odd = [placed(x, 0) for x in parts], [placed(x, at) for x, at in zip(parts, (1, 3, 7))]
+    base = torch.randn(M, N, generator=g)
+    for epi in (cf.EPI_STORE_F32, cf.EPI_ADD_F32, cf.EPI_STORE_T, cf.EPI_SILU_MUL):
+        for impl in (0, 3, 4, 5) if K % 64 == 0 else (0,):
+            outs = []
+            for a, w, w2 in (even, odd, (even[0], odd[1], even[2]), (odd[0], even[1], odd[2])):
+                out = base.cuda() if epi in (cf.EPI_STORE_F32, cf.EPI_ADD_F32) else base.bfloat16().cuda()
+                p, as_float = out.data_ptr(), out.dtype == torch.float32
+                sess.ctx.op_gemm(a.data_ptr(), w.data_ptr(), w2.data_ptr(), p if as_float else 0, 0 if as_float else p,
+                                 M, N, K, epi, impl)
+                outs.append(out)
+            assert not bool(torch.isnan(outs[0].float()).any())
+            assert all(torch.equal(outs[0], o) for o in outs[1:]), f"epilogue {epi}, impl {impl}"
+
+
+@pytest.mark.parametrize("impl", [0, 3, 4])
+def test_gemm_rows_that_pass_the_32_bit_offsets(sess, impl):
+    """256 rows of 2^23 elements are 2^32 bytes, more than a tile's 32-bit offsets reach.  Few entries are not
+    zero, so the sums are whole numbers and exact."""
+    import paper_2604_25080_amd as cf
+    M, N, K = 256, 256, 1 << 23
+    A, W = (torch.zeros(r, K, dtype=torch.bfloat16, device="cuda") for r in (M, N))
+    cols = [0, 7, 64, 4099, (1 << 22) - 1, 1 << 22, K - 65, K - 1]
+    g = torch.Generator().manual_seed(3)
+    a, w = (torch.randint(-4, 5, (r, len(cols)), generator=g).float() for r in (M, N))
+    A[:, cols], W[:, cols] = a.bfloat16().cuda(), w.bfloat16().cuda()
+    Cf = torch.full((M, N), float("nan"), device="cuda")
+    sess.ctx.op_gemm(A.data_ptr(), W.data_ptr(), 0, Cf.data_ptr(), 0, M, N, K, cf.EPI_STORE_F32, impl)
+    assert torch.equal(Cf.cpu(), a @ w.t())
 
 
 def test_gemm_mfma_refuses_what_it_cannot_tile(sess):
