@@ -68,10 +68,10 @@ __device__ __forceinline__ u32x4_t buffer_rsrc(const void* base, unsigned bytes)
 }
 constexpr unsigned PAST_THE_END = 0x80000000u;    // no operand tile is that long: such an offset reads zero
 // 16 bytes per lane from the buffer straight to LDS: lane i lands at lds + 16 i.  No register is
-// written; whoever reads the LDS bytes waits for vmcnt first (wait_barrier below).
+// written; whoever reads the LDS bytes waits for vmcnt first (wait_barrier below).  The LDS base goes in
+// m0, which the compiler sets (an operand, not a write it does not know of).
 __device__ __forceinline__ void load_to_lds(u32x4_t rsrc, unsigned voff, unsigned soff, unsigned lds) {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds) : "memory");
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" :: "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds) : "memory");
 }
 // This wavefront's LDS reads are done and all but its last LEFT loads have landed; then everybody's.
 template <int LEFT>
