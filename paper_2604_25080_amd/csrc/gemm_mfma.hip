@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "per_device.h"
 #include "rope.h"
 #include "cacheflow.h"
 
@@ -701,6 +702,13 @@ gemm_rows_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W, float* 
 constexpr int N_CUS = 256;            // MI355X
 constexpr int GROUP_M = 8;            // tile rows per group of the tile order (see the body)
 
+// Lets a kernel have `bytes` of LDS: an attribute of the kernel on one device.
+void allow_lds(PerDevice& once, const void* kern, int bytes) {
+    int device = -1;
+    (void)hipGetDevice(&device);
+    once.run(device, [&] { (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
+
 template <int EPI, int B, bool DIRECT>
 void launch_tile(hipStream_t s, const void* A, const void* W, const void* W2, float* Cf, void* Dt,
                  int M, int N, int K, bool tail_ok = false, const RopeEpilogue& rope = RopeEpilogue{}) {
@@ -713,12 +721,9 @@ void launch_tile(hipStream_t s, const void* A, const void* W, const void* W2, fl
         const int gsz = tiles_m - (tiles_m - 1) / GROUP_M * GROUP_M;       // rows of the last group
         const int cols = (tail + gsz - 1) / gsz;
         if (tail_ok && nb > N_CUS && tail > 0 && gsz * cols <= N_CUS / 2 && cols <= tiles_n) {
-            static bool configured = false;
+            static PerDevice configured;
             auto kern = gemm_mfma_tail_kernel<EPI>;
-            if (!configured) {
-                (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-                configured = true;
-            }
+            allow_lds(configured, (const void*)kern, LDS);
             constexpr int SBN_OUT = (EPI == EPI_SILU_MUL) ? 64 : 128;
             const int m_off = (tiles_m - gsz) * B, n_off = (tiles_n - cols) * BN_OUT;
             const int tm = (M - m_off + 127) / 128, tn = (N - n_off + SBN_OUT - 1) / SBN_OUT;
@@ -728,12 +733,9 @@ void launch_tile(hipStream_t s, const void* A, const void* W, const void* W2, fl
             return;
         }
     }
-    static bool configured = false;
+    static PerDevice configured;
     auto kern = gemm_mfma_kernel<EPI, B, DIRECT>;
-    if (!configured) {
-        (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        configured = true;
-    }
+    allow_lds(configured, (const void*)kern, LDS);
     kern<<<tiles_m * tiles_n, 64 * Tile<B, DIRECT>::NWM * Tile<B, DIRECT>::NWN, LDS, s>>>((const bf16*)A, (const bf16*)W, (const bf16*)W2, Cf,
                                              (bf16*)Dt, M, N, K, tiles_m, tiles_n, rope);
 }
@@ -741,12 +743,9 @@ void launch_tile(hipStream_t s, const void* A, const void* W, const void* W2, fl
 template <int EPI, int BM, int BN, int G, int S>
 void launch_rows(hipStream_t s, const void* A, const void* W, float* Cf, void* Dt, int M, int N, int K) {
     constexpr int LDS = S * G * (BM + BN) * ROW_BYTES;
-    static bool configured = false;
+    static PerDevice configured;
     auto kern = gemm_rows_kernel<EPI, BM, BN, G, S>;
-    if (!configured) {
-        (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        configured = true;
-    }
+    allow_lds(configured, (const void*)kern, LDS);
     kern<<<(N + BN - 1) / BN, BM == 16 ? 128 : 256, LDS, s>>>((const bf16*)A, (const bf16*)W, Cf, (bf16*)Dt, M, N, K);
 }
 
