@@ -150,6 +150,62 @@ def test_gemm_few_rows_and_ragged_k(sess, rows, nk):
         assert bool((err <= bound).all())
 
 
+def _placed(x, rows, K):
+    """The first rows of x [M, K] on the device, NaN behind them."""
+    t = torch.full((rows * K + 64,), float("nan")).bfloat16()
+    t[:rows * K] = x[:rows].reshape(-1)
+    return t.cuda()
+
+
+@pytest.mark.parametrize("K", [72, 712])
+def test_gemm_ragged_k_on_the_128_tile(sess, K):
+    """1700 x 2000 is more than three 64-wide tiles per CU: the 128x128 tile, with a last K-step that is partly
+    past the rows' end.  2^-24 per term against float64, and the bits that 65 rows get on the 64 tile."""
+    import paper_2604_25080_amd as cf
+    M, N, few = 1700, 2000, 65
+    g = torch.Generator().manual_seed(K)
+    x, y, y2 = ((torch.randn(r, K, generator=g) * std).bfloat16() for r, std in ((M, 1.0), (N, 0.05), (N, 0.05)))
+    A, Few, W, W2 = _placed(x, M, K), _placed(x, few, K), _placed(y, N, K), _placed(y2, N, K)
+    x, y, y2 = x.double(), y.double(), y2.double()
+    ref, ref2 = x @ y.t(), x @ y2.t()
+    for epi in (cf.EPI_STORE_F32, cf.EPI_SILU_MUL):
+        as_float = epi == cf.EPI_STORE_F32
+        outs = []
+        for src, m in ((A, M), (Few, few)):
+            out = torch.zeros(m, N, dtype=torch.float32 if as_float else torch.bfloat16, device="cuda")
+            p = out.data_ptr()
+            sess.ctx.op_gemm(src.data_ptr(), W.data_ptr(), W2.data_ptr(), p if as_float else 0, 0 if as_float else p, m, N, K, epi)
+            outs.append(out)
+        assert torch.equal(outs[0][:few], outs[1])
+        r = ref if as_float else ref * torch.sigmoid(ref) * ref2
+        bound = K * 2.0 ** -24 * (x.abs() @ y.abs().t()) if as_float else 2.0 ** -8 * r.abs() + 1e-5
+        assert bool(((outs[0].cpu().double() - r).abs() <= bound).all())
+
+
+# 16 tile columns: 336, 368 and 384 big tiles, 80, 112 and 128 of them past the first round
+@pytest.mark.parametrize("tiles_m, K", [(21, 1024), (23, 1152), (24, 2048)])
+def test_gemm_quartered_tail_over_long_k(sess, tiles_m, K):
+    """The tail's 128x128 tiles with more K-steps than their ring holds, up to half a round of them, ragged in M
+    (and N): the bits of the plain launch of big tiles, and 2^-24 per term against float64."""
+    import paper_2604_25080_amd as cf
+    M = tiles_m * 256 - 5
+    g = torch.Generator("cuda").manual_seed(M + K)
+    mat = lambda r, std: (torch.randn(r, K, generator=g, device="cuda") * std).bfloat16()  # noqa: E731
+    a = mat(M, 1.0)
+    for epi, N in ((cf.EPI_STORE_F32, 4090), (cf.EPI_STORE_T, 4096), (cf.EPI_SILU_MUL, 2044)):
+        w, w2 = mat(N, 0.05), mat(N, 0.05)
+        outs = []
+        for impl in (3, 6):
+            out = torch.full((M, N), float("nan"), dtype=torch.float32 if epi == cf.EPI_STORE_F32 else torch.bfloat16, device="cuda")
+            p, as_float = out.data_ptr(), epi == cf.EPI_STORE_F32
+            sess.ctx.op_gemm(a.data_ptr(), w.data_ptr(), w2.data_ptr(), p if as_float else 0, 0 if as_float else p, M, N, K, epi, impl)
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1])
+        if epi == cf.EPI_STORE_F32:
+            x, y = a.double(), w.double()
+            assert bool(((outs[1].double() - x @ y.t()).abs() <= K * 2.0 ** -24 * (x.abs() @ y.abs().t())).all())
+
+
 @pytest.mark.parametrize("at_a, at_w", [(2, 0), (0, 6), (1, 0), (0, 3)])
 def test_gemm_operands_that_start_inside_a_larger_buffer(sess, at_a, at_w):
     """Whole-dword starts are loaded straight to LDS, odd elements through registers; 2^-24 per term."""
