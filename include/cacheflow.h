@@ -669,7 +669,10 @@ int cf_read_final_hidden(cf_ctx* ctx, int32_t B, float* out_host);
  * layer from the bottom, and only the attention of the new-turn rows of layer l
  * waits for layer l's loads, so the first-token prefill overlaps restoration.
  * on == 0: sequential join -- recompute || load (top layer first), then wait
- * for both, then the new-turn prefill.  Results are identical.               */
+ * for both, then the new-turn prefill.  Results are identical, except for the
+ * rounding of rows at positions from 2048 on: where a launch holds too few rows
+ * to fill the GPU the key range of such rows is split, and the two modes may
+ * divide the rows into launches (of chunk_rows) differently.                */
 int cf_ctx_set_pipelined_join(cf_ctx* ctx, int32_t on);
 
 /* Load path (the I/O side of Sec. 3.1's two pointers).  path 0 (default):
